@@ -9,10 +9,12 @@
 // semantic.cpp) writes that predecessor table once per plan, and the
 // transposed table of consumers, which the backward walks to gather each
 // row's gradient.
-//   k_conv_fwd      one thread per (4 channels, run of 32 rows);
-//   k_conv_bwd      runs of 64 rows: dx of each row (its own term plus
-//                   every consumer's, in (tap, row) order) and the run's
-//                   tap sums x[pred_i(r)] dy[r], in row order;
+//   k_conv_fwd      one thread per (4 channels, sub-run of 16 rows);
+//   k_conv_bwd      the same threads, four sub-runs to a run of 64 rows: dx
+//                   of each row (its own term plus every consumer's, in
+//                   (tap, row) order) and the run's tap sums
+//                   x[pred_i(r)] dy[r], in row order within a sub-run, the
+//                   sub-runs added in order;
 //   k_conv_dw_sum   per (channel, tap), the runs' partials in a fixed order.
 // Arithmetic in float32; no atomics, so reruns are bitwise identical.
 #include <hip/hip_runtime.h>
@@ -32,9 +34,12 @@ namespace {
 typedef __bf16 bf16;
 constexpr int CV_THR = 256;
 constexpr int CV_MAXW = 8;
-constexpr int CV_RUN = 32;     // rows per thread in the forward
-constexpr int CV_RUN_B = 64;   // rows per thread in the backward (one partial dW per run)
-constexpr int CV_SUCC = 2048;  // consumer entries of a backward run staged in LDS
+constexpr int CV_SUB = 4;                     // sub-runs (waves) of a workgroup
+constexpr int CV_RT = 16;                     // rows of a sub-run
+constexpr int CV_RUN = CV_SUB * CV_RT;        // rows of a run (one partial dW per run)
+constexpr int CV_G = 4;                       // rows taken at a time
+constexpr int CV_SUCC = 1024;                 // consumer entries of a run staged in LDS
+static_assert(CV_SUB * 64 == CV_THR && CV_RUN == 64 && CV_RT % CV_G == 0, "one wave per sub-run, one lane per row");
 
 template <typename T> struct CV;
 template <> struct CV<bf16> {
@@ -69,12 +74,25 @@ template <> struct CV<float> {
   }
 };
 
-// Threads own 4 channels each (consecutive threads,
-// consecutive vectors of the same rows: coalesced) and walk a run of rows,
-// with their W taps in registers.  Inside a segment a row's predecessors
-// are the rows just before it, so the activations of the previous rows are
-// kept in registers and reloaded only where the table points elsewhere
-// (a segment's first rows, whose window reaches into an ancestor).
+// A workgroup takes a run of 64 rows for 64 vectors of 4 channels: wave s the
+// rows of sub-run s, lane l vector l of the block (a row of a wave is one
+// contiguous piece of 512 or 1024 bytes), the W taps in registers.  These
+// kernels only stream, so what bounds them is how many bytes a CU has in
+// flight: a wave requests the next CV_G rows before it uses the present ones,
+// and short sub-runs give a small call enough waves.  Measured against one
+// thread per whole run (64 rows backward, 32 forward), every row through the
+// tables: backward of 68,161 x 6,144 bf16, w = 4: 792 -> 566 us (4.4 TB/s of
+// x, dy and dx), of 3,001 x 1,000 float32, w = 3 (47 workgroups before):
+// 53.9 -> 17.7 us; forward 325 -> 316 and 14.4 -> 8.1 us.  Sub-runs of 32
+// rows: 544 and 22.3 us, of 8 rows: 809 and 17.6; two rows at a time: 597 and
+// 15.2 us.
+//
+// A row is regular when its predecessors are the rows just above it and, in
+// the backward, its consumers exactly the rows just below it: all rows of a
+// segment but the first and last W - 1.  Rows are taken CV_G at a time; a
+// group of regular rows needs no tables and no branches, its windows over x
+// and dy stay in registers.  Any other group takes its rows one by one, every
+// tap and consumer through the tables.  Both add in the same order.
 template <typename T, int W>
 __device__ inline void load_taps(const float* __restrict__ Wt, int c0, float (&wt)[W][CV<T>::N]) {
 #pragma unroll
@@ -93,18 +111,11 @@ __device__ inline void load_taps(const float* __restrict__ Wt, int c0, float (&w
   }
 }
 
-// v <- x[pred_i(r)] (tap i >= 1): from the registers of the previous rows
-// when the predecessor is the row i above in this thread's run, else loaded
-// (zero before the trajectory start or for an invalid entry).
-// hist[j] = x[r - 1 - j].
-template <typename T, int W>
-__device__ inline void tap_value(const T* __restrict__ x, int64_t C, int Cch, int c0, int64_t r,
-                                 int64_t run0, int i, int32_t p, const float (&hist)[W - 1][CV<T>::N],
-                                 float (&v)[CV<T>::N]) {
-  if (p == r - i && r - i >= run0) {
-#pragma unroll
-    for (int e = 0; e < CV<T>::N; ++e) v[e] = hist[i - 1][e];
-  } else if (p >= 0 && p < C) {
+// v <- x[p] (zero before the trajectory start or for an invalid entry)
+template <typename T>
+__device__ inline void load_row(const T* __restrict__ x, int64_t C, int Cch, int c0, int32_t p,
+                                float (&v)[CV<T>::N]) {
+  if (p >= 0 && p < C) {
     CV<T>::load(x + static_cast<int64_t>(p) * Cch + c0, v);
   } else {
 #pragma unroll
@@ -112,14 +123,25 @@ __device__ inline void tap_value(const T* __restrict__ x, int64_t C, int Cch, in
   }
 }
 
-template <typename T, int W>
-__device__ inline void shift_hist(float (&hist)[W - 1][CV<T>::N], const float (&cur)[CV<T>::N]) {
+// The row's predecessors are the W - 1 rows just above it.
+template <int W>
+__device__ inline bool regular_pred(const int32_t* pr, int64_t r) {
+  bool ok = r >= W - 1;
 #pragma unroll
-  for (int j = W - 2; j > 0; --j)
+  for (int i = 1; i < W; ++i) ok &= pr[i - 1] == r - i;
+  return ok;
+}
+
+// Bit g of the result: rows CV_G g .. CV_G g + CV_G - 1 of the sub-run (first
+// row f of the run, n rows) are all in the run's mask of regular rows.
+__device__ inline uint32_t regular_groups(unsigned long long rows, int f, int n) {
+  uint32_t m = 0;
 #pragma unroll
-    for (int e = 0; e < CV<T>::N; ++e) hist[j][e] = hist[j - 1][e];
-#pragma unroll
-  for (int e = 0; e < CV<T>::N; ++e) hist[0][e] = cur[e];
+  for (int g = 0; g < CV_RT / CV_G; ++g) {
+    const uint32_t four = static_cast<uint32_t>(rows >> (f + CV_G * g)) & ((1u << CV_G) - 1u);
+    m |= (four == (1u << CV_G) - 1u && CV_G * (g + 1) <= n ? 1u : 0u) << g;
+  }
+  return __builtin_amdgcn_readfirstlane(m);
 }
 
 template <typename T, int W>
@@ -127,7 +149,9 @@ __global__ __launch_bounds__(CV_THR) void k_conv_fwd(int64_t C, int Cch, const T
                                                      const float* __restrict__ Wt,
                                                      const int32_t* __restrict__ pred, T* __restrict__ y) {
   using V = CV<T>;
-  const int vec = blockIdx.x * CV_THR + threadIdx.x;
+  using Raw = typename V::Raw;
+  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  const int vec = blockIdx.x * 64 + lane;
   const int c0 = vec * V::N;
   const int64_t r0 = static_cast<int64_t>(blockIdx.y) * CV_RUN;
   const int64_t r1 = r0 + CV_RUN < C ? r0 + CV_RUN : C;
@@ -136,31 +160,70 @@ __global__ __launch_bounds__(CV_THR) void k_conv_fwd(int64_t C, int Cch, const T
   __shared__ int32_t s_pred[CV_RUN * (W - 1)];
   for (int j = threadIdx.x; j < (r1 - r0) * (W - 1); j += CV_THR) s_pred[j] = pred[r0 * (W - 1) + j];
   __syncthreads();
-  if (vec >= Cch / V::N) return;
-  float wt[W][V::N], hist[W - 1][V::N];
+  const unsigned long long rows =
+      __ballot(r0 + lane < r1 && regular_pred<W>(s_pred + lane * (W - 1), r0 + lane));
+  const int64_t rs = r0 + sub * CV_RT;
+  const int n = static_cast<int>(r1 - rs < CV_RT ? r1 - rs : CV_RT);
+  if (vec >= Cch / V::N || n <= 0) return;
+  const uint32_t fast = regular_groups(rows, sub * CV_RT, n);
+  float wt[W][V::N];
   load_taps<T, W>(Wt, c0, wt);
-  for (int64_t r = r0; r < r1; ++r) {
-    float cur[V::N], v[V::N], acc[V::N];
-    V::load(x + r * Cch + c0, cur);
+  // xw[j] = x[row - (W - 1) + j] as loaded; requests past either end are
+  // clamped and never used (a regular row's window lies inside the tensor)
+  Raw xw[W - 1 + CV_G];
 #pragma unroll
-    for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * cur[e];
+  for (int j = 0; j < W - 1 + CV_G; ++j) {
+    const int64_t r = rs - (W - 1) + j;
+    xw[j] = V::raw(x + (r < 0 ? 0 : (r < C ? r : C - 1)) * Cch + c0);
+  }
+  for (int g = 0; CV_G * g < n; ++g) {
+    const int64_t r = rs + CV_G * g;
+    // (guarded, the loads past a sub-run's end cost 5% of the forward;
+    // guarding them in the backward made it 4% slower)
+    Raw xn[CV_G];
 #pragma unroll
-    for (int i = 1; i < W; ++i) {
-      tap_value<T, W>(x, C, Cch, c0, r, r0, i, s_pred[(r - r0) * (W - 1) + i - 1], hist, v);
+    for (int q = 0; q < CV_G; ++q)
+      if (CV_G * (g + 1) < n) xn[q] = V::raw(x + (r + CV_G + q < C ? r + CV_G + q : C - 1) * Cch + c0);
+    if (fast >> g & 1u) {
 #pragma unroll
-      for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
+      for (int q = 0; q < CV_G; ++q) {
+        float v[V::N], acc[V::N];
+        V::cvt(xw[W - 1 + q], v);
+#pragma unroll
+        for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * v[e];
+#pragma unroll
+        for (int i = 1; i < W; ++i) {
+          V::cvt(xw[W - 1 + q - i], v);
+#pragma unroll
+          for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
+        }
+        V::store(y + (r + q) * Cch + c0, acc);
+      }
+    } else {
+      const int64_t re = r + CV_G < rs + n ? r + CV_G : rs + n;
+      for (int64_t rr = r; rr < re; ++rr) {
+        float v[V::N], acc[V::N];
+        V::load(x + rr * Cch + c0, v);
+#pragma unroll
+        for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * v[e];
+#pragma unroll
+        for (int i = 1; i < W; ++i) {
+          load_row<T>(x, C, Cch, c0, s_pred[(rr - r0) * (W - 1) + i - 1], v);
+#pragma unroll
+          for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
+        }
+        V::store(y + rr * Cch + c0, acc);
+      }
     }
-    V::store(y + r * Cch + c0, acc);
-    shift_hist<T, W>(hist, cur);
+#pragma unroll
+    for (int j = 0; j < W - 1; ++j) xw[j] = xw[CV_G + j];
+#pragma unroll
+    for (int q = 0; q < CV_G; ++q) xw[W - 1 + q] = xn[q];
   }
 }
 
 // dx of a run of rows, and the run's partial weight gradient:
-// part[run][c][i] = sum over the run's rows r of x[pred_i(r)][c] dy[r][c].
-// Inside a segment the consumers of row r through tap i are the rows r + i,
-// so dy of the next W - 1 rows rides along in registers (one new row
-// loaded per step) and only consumers elsewhere (the first rows of child
-// segments) are loaded through the table.
+// part[run][i][c] = sum over the run's rows r of x[pred_i(r)][c] dy[r][c].
 template <typename T, int W>
 __global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T* __restrict__ x,
                                                      const float* __restrict__ Wt,
@@ -170,17 +233,20 @@ __global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T
                                                      const T* __restrict__ dy, T* __restrict__ dx,
                                                      float* __restrict__ part) {
   using V = CV<T>;
-  const int vec = blockIdx.x * CV_THR + threadIdx.x;
+  using Raw = typename V::Raw;
+  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  const int vec = blockIdx.x * 64 + lane;
   const int c0 = vec * V::N;
-  const int64_t r0 = static_cast<int64_t>(blockIdx.y) * CV_RUN_B;
-  const int64_t r1 = r0 + CV_RUN_B < C ? r0 + CV_RUN_B : C;
+  const int64_t r0 = static_cast<int64_t>(blockIdx.y) * CV_RUN;
+  const int64_t r1 = r0 + CV_RUN < C ? r0 + CV_RUN : C;
   // the run's tables, staged in LDS: predecessors, consumer offsets
   // (relative to the run's first entry) and up to CV_SUCC consumer entries;
   // entries beyond that (rows feeding very many children) are read from
   // global memory
-  __shared__ int32_t s_pred[CV_RUN_B * (W - 1)];
-  __shared__ int32_t s_off[CV_RUN_B + 1];
+  __shared__ int32_t s_pred[CV_RUN * (W - 1)];
+  __shared__ int32_t s_off[CV_RUN + 1];
   __shared__ int32_t s_succ[CV_SUCC];
+  __shared__ float4 s_gw[CV_SUB][W][64];
   const int64_t nr = r1 - r0;
   const int64_t b0 = succ_off[r0] < 0 ? 0 : (succ_off[r0] > n_succ ? n_succ : succ_off[r0]);
   for (int j = threadIdx.x; j < nr * (W - 1); j += CV_THR) s_pred[j] = pred[r0 * (W - 1) + j];
@@ -193,82 +259,135 @@ __global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T
   const int32_t n_run_succ = s_off[nr];
   for (int j = threadIdx.x; j < n_run_succ && j < CV_SUCC; j += CV_THR) s_succ[j] = succ[b0 + j];
   __syncthreads();
-  if (vec >= Cch / V::N) return;
-  float wt[W][V::N], hist[W - 1][V::N], gw[W][V::N];
-  load_taps<T, W>(Wt, c0, wt);
+  bool reg = false;
+  if (lane < nr) {
+    const int64_t r = r0 + lane;
+    const int32_t jb = s_off[lane];
+    reg = regular_pred<W>(s_pred + lane * (W - 1), r) && r + W - 1 < C && s_off[lane + 1] == jb + W - 1 &&
+          jb + W - 1 <= CV_SUCC;
+    if (reg) {
+#pragma unroll
+      for (int i = 1; i < W; ++i) reg &= s_succ[jb + i - 1] == (r + i) * 8 + i;
+    }
+  }
+  const unsigned long long rows = __ballot(reg);
+  const int64_t rs = r0 + sub * CV_RT;
+  const int n = static_cast<int>(r1 - rs < CV_RT ? r1 - rs : CV_RT);
+  const bool live = vec < Cch / V::N;
+  float gw[W][V::N];
 #pragma unroll
   for (int i = 0; i < W; ++i)
 #pragma unroll
     for (int e = 0; e < V::N; ++e) gw[i][e] = 0.f;
-  // dr[i] = dy[r + i] as loaded, one row beyond the window, so that the
-  // window's rows are widened at the top of a row while only the row beyond
-  // it and the next row's x are in flight.  Every load is unconditional:
-  // past the last row the last row is requested again, an entry never used
-  // (the consumers of a row are rows of the table).
-  using Raw = typename V::Raw;
-  Raw dr[W + 1];
+  if (live && n > 0) {
+    const uint32_t fast = regular_groups(rows, sub * CV_RT, n);
+    float wt[W][V::N];
+    load_taps<T, W>(Wt, c0, wt);
+    // windows as loaded: xw[j] = x[row - (W - 1) + j], dw[j] = dy[row + j];
+    // requests past either end are clamped and never used (a regular row's
+    // windows lie inside the tensors)
+    Raw xw[W - 1 + CV_G], dw[W - 1 + CV_G];
 #pragma unroll
-  for (int i = 0; i <= W; ++i) dr[i] = V::raw(dy + (r0 + i < C ? r0 + i : C - 1) * Cch + c0);
-  Raw xr = V::raw(x + r0 * Cch + c0);   // x of the row, requested a row ahead
-  for (int64_t r = r0; r < r1; ++r) {
-    float cur[V::N], dwin[W][V::N], v[V::N], acc[V::N];
-    V::cvt(xr, cur);
-#pragma unroll
-    for (int k = 0; k < W; ++k) V::cvt(dr[k], dwin[k]);
-    xr = V::raw(x + (r + 1 < C ? r + 1 : C - 1) * Cch + c0);
-#pragma unroll
-    for (int e = 0; e < V::N; ++e) {
-      acc[e] = wt[0][e] * dwin[0][e];
-      gw[0][e] += cur[e] * dwin[0][e];
+    for (int j = 0; j < W - 1 + CV_G; ++j) {
+      const int64_t rx = rs - (W - 1) + j, rd = rs + j;
+      xw[j] = V::raw(x + (rx < 0 ? 0 : (rx < C ? rx : C - 1)) * Cch + c0);
+      dw[j] = V::raw(dy + (rd < C ? rd : C - 1) * Cch + c0);
     }
+    for (int g = 0; CV_G * g < n; ++g) {
+      const int64_t r = rs + CV_G * g;
+      Raw xn[CV_G], dn[CV_G];
 #pragma unroll
-    for (int i = 1; i < W; ++i) {
-      tap_value<T, W>(x, C, Cch, c0, r, r0, i, s_pred[(r - r0) * (W - 1) + i - 1], hist, v);
-#pragma unroll
-      for (int e = 0; e < V::N; ++e) gw[i][e] += v[e] * dwin[0][e];
-    }
-    // consumers in table order: the staged entries from LDS, any beyond
-    // them from global memory (two loops, so that neither read goes through
-    // a flat address that would wait for every outstanding load)
-    const auto consume = [&](int32_t code) __attribute__((always_inline)) {
-      const int32_t sr = code >> 3, i = code & 7;  // consumer row, tap
-      if (sr < 0 || sr >= C || i < 1 || i >= W) return;
-      if (sr == r + i) {  // the row i below: already in registers
-#pragma unroll
-        for (int k = 1; k < W; ++k)
-          if (k == i) {
-#pragma unroll
-            for (int e = 0; e < V::N; ++e) acc[e] += wt[k][e] * dwin[k][e];
-          }
-      } else {
-        V::load(dy + static_cast<int64_t>(sr) * Cch + c0, v);
-#pragma unroll
-        for (int k = 1; k < W; ++k)
-          if (k == i) {
-#pragma unroll
-            for (int e = 0; e < V::N; ++e) acc[e] += wt[k][e] * v[e];
-          }
+      for (int q = 0; q < CV_G; ++q) {
+        const int64_t rx = r + CV_G + q, rd = rx + W - 1;
+        xn[q] = V::raw(x + (rx < C ? rx : C - 1) * Cch + c0);
+        dn[q] = V::raw(dy + (rd < C ? rd : C - 1) * Cch + c0);
       }
-    };
-    const int32_t jb = s_off[r - r0], je = s_off[r - r0 + 1];
-    const int32_t jl = je < CV_SUCC ? je : CV_SUCC;
-    for (int32_t j = jb; j < jl; ++j) consume(s_succ[j]);
-    for (int32_t j = jb > CV_SUCC ? jb : CV_SUCC; j < je; ++j) consume(succ[b0 + j]);
-    V::store(dx + r * Cch + c0, acc);
-    shift_hist<T, W>(hist, cur);
+      if (fast >> g & 1u) {
 #pragma unroll
-    for (int k = 0; k < W; ++k) dr[k] = dr[k + 1];
-    dr[W] = V::raw(dy + (r + W + 1 < C ? r + W + 1 : C - 1) * Cch + c0);
+        for (int q = 0; q < CV_G; ++q) {
+          float d0[V::N], v[V::N], acc[V::N];
+          V::cvt(dw[q], d0);
+#pragma unroll
+          for (int i = 0; i < W; ++i) {
+            V::cvt(xw[W - 1 + q - i], v);
+#pragma unroll
+            for (int e = 0; e < V::N; ++e) gw[i][e] += v[e] * d0[e];
+          }
+#pragma unroll
+          for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * d0[e];
+#pragma unroll
+          for (int i = 1; i < W; ++i) {
+            V::cvt(dw[q + i], v);
+#pragma unroll
+            for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
+          }
+          V::store(dx + (r + q) * Cch + c0, acc);
+        }
+      } else {
+        const int64_t re = r + CV_G < rs + n ? r + CV_G : rs + n;
+        for (int64_t rr = r; rr < re; ++rr) {
+          float d0[V::N], v[V::N], acc[V::N];
+          V::load(dy + rr * Cch + c0, d0);
+          V::load(x + rr * Cch + c0, v);
+#pragma unroll
+          for (int e = 0; e < V::N; ++e) {
+            acc[e] = wt[0][e] * d0[e];
+            gw[0][e] += v[e] * d0[e];
+          }
+#pragma unroll
+          for (int i = 1; i < W; ++i) {
+            load_row<T>(x, C, Cch, c0, s_pred[(rr - r0) * (W - 1) + i - 1], v);
+#pragma unroll
+            for (int e = 0; e < V::N; ++e) gw[i][e] += v[e] * d0[e];
+          }
+          // consumers in table order: the staged entries from LDS, any
+          // beyond them from global memory
+          const int32_t jb = s_off[rr - r0], je = s_off[rr - r0 + 1];
+          for (int32_t j = jb; j < je; ++j) {
+            int32_t code;
+            if (j < CV_SUCC) code = s_succ[j];
+            else code = succ[b0 + j];
+            const int32_t sr = code >> 3, i = code & 7;  // consumer row, tap
+            if (sr < 0 || sr >= C || i < 1 || i >= W) continue;
+            V::load(dy + static_cast<int64_t>(sr) * Cch + c0, v);
+#pragma unroll
+            for (int k = 1; k < W; ++k)
+              if (k == i) {
+#pragma unroll
+                for (int e = 0; e < V::N; ++e) acc[e] += wt[k][e] * v[e];
+              }
+          }
+          V::store(dx + rr * Cch + c0, acc);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < W - 1; ++j) {
+        xw[j] = xw[CV_G + j];
+        dw[j] = dw[CV_G + j];
+      }
+#pragma unroll
+      for (int q = 0; q < CV_G; ++q) {
+        xw[W - 1 + q] = xn[q];
+        dw[W - 1 + q] = dn[q];
+      }
+    }
   }
+  // the sub-runs' tap sums, added in order; the waves share the taps
+#pragma unroll
+  for (int i = 0; i < W; ++i) s_gw[sub][i][lane] = float4{gw[i][0], gw[i][1], gw[i][2], gw[i][3]};
+  __syncthreads();
   // partials tap-major ([run][tap][channel]): every store is a coalesced
-  // 16- or 32-byte piece of one tap's channel row
+  // piece of one tap's channel row
   float* out = part + static_cast<int64_t>(blockIdx.y) * Cch * W;
+  for (int i = sub; i < W && live; i += CV_SUB) {
+    float4 a = s_gw[0][i][lane];
 #pragma unroll
-  for (int i = 0; i < W; ++i)
-#pragma unroll
-    for (int e = 0; e < V::N; e += 4)
-      *reinterpret_cast<float4*>(out + static_cast<int64_t>(i) * Cch + c0 + e) =
-          float4{gw[i][e], gw[i][e + 1], gw[i][e + 2], gw[i][e + 3]};
+    for (int k = 1; k < CV_SUB; ++k) {
+      const float4 b = s_gw[k][i][lane];
+      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    *reinterpret_cast<float4*>(out + static_cast<int64_t>(i) * Cch + c0) = a;
+  }
 }
 
 // dW[c][i] = sum over runs of part[run][i][c]: a workgroup takes 32
@@ -284,8 +403,12 @@ __global__ __launch_bounds__(CV_THR) void k_conv_dw_sum(int64_t n_run, int Cch, 
   const int64_t n = static_cast<int64_t>(Cch) * W;
   const int64_t k = static_cast<int64_t>(blockIdx.x) * DW_K + lk;  // i * Cch + c
   float acc = 0.f;
-  if (k < n)
+  if (k < n) {
+    // eight partials requested together: 59 -> 27 us for the 1,066 runs of a
+    // 68,161 x 6,144 call, w = 4 (105 MB)
+#pragma unroll 8
     for (int64_t b = g; b < n_run; b += DW_G) acc += part[b * n + k];
+  }
   red[g][lk] = acc;
   __syncthreads();
   if (g == 0 && k < n) {
@@ -324,7 +447,7 @@ template <typename T>
 int launch_fwd(int w, int64_t C, int Cch, const void* x, const float* Wt, const int32_t* pred, void* y,
                hipStream_t s) {
   const int nvec = Cch / CV<T>::N;
-  const dim3 grid(static_cast<uint32_t>((nvec + CV_THR - 1) / CV_THR),
+  const dim3 grid(static_cast<uint32_t>((nvec + 63) / 64),
                   static_cast<uint32_t>((C + CV_RUN - 1) / CV_RUN));
   const T* xx = static_cast<const T*>(x);
   T* yy = static_cast<T*>(y);
@@ -343,8 +466,8 @@ int launch_bwd(int w, int64_t C, int Cch, const void* x, const float* Wt, const 
                const int64_t* succ_off, const int32_t* succ, int64_t n_succ, const void* dy, void* dx,
                float* dW, float* part, hipStream_t s) {
   const int nvec = Cch / CV<T>::N;
-  const int64_t n_run = (C + CV_RUN_B - 1) / CV_RUN_B;
-  const dim3 grid(static_cast<uint32_t>((nvec + CV_THR - 1) / CV_THR), static_cast<uint32_t>(n_run));
+  const int64_t n_run = (C + CV_RUN - 1) / CV_RUN;
+  const dim3 grid(static_cast<uint32_t>((nvec + 63) / 64), static_cast<uint32_t>(n_run));
   const T* xx = static_cast<const T*>(x);
   const T* gy = static_cast<const T*>(dy);
   T* gx = static_cast<T*>(dx);
@@ -373,7 +496,7 @@ using namespace harts;
 extern "C" int harts_conv_workspace_size(int64_t C, int32_t Cch, int32_t w, size_t* bytes) {
   if (int rc = check_conv(HARTS_F32, C, Cch, w, "harts_conv_workspace_size")) return rc;
   if (!bytes) { set_error("harts_conv_workspace_size: NULL bytes"); return HARTS_EINVAL; }
-  const int64_t n_run = (C + CV_RUN_B - 1) / CV_RUN_B;
+  const int64_t n_run = (C + CV_RUN - 1) / CV_RUN;
   *bytes = static_cast<size_t>(std::max<int64_t>(n_run, 1)) * Cch * w * sizeof(float);
   return HARTS_OK;
 }

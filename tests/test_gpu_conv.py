@@ -108,6 +108,50 @@ def test_conv_matches_oracle_small(L, label, parent, seg_len, w, dtype):
     assert all(e <= TOL[dtype] for e in errs.values()), errs
 
 
+# Edges of the kernels' runs (64 rows), sub-runs (16), groups (4) and channel
+# blocks (256), rows with more consumers than a run stages in LDS, and widths
+# whose windows reach over several short ancestors.
+EDGES = [
+    ("one row", [-1], [1], 8, 3),
+    ("15, 16 and 17 rows", [-1, -1, -1], [15, 16, 17], 264, 5),
+    ("63, 64, 65 rows in a chain", [-1, 0, 0], [63, 64, 65], 256, 4),
+    ("segments of 1 to 7 rows", [-1] + list(range(60)), [1 + (5 * i) % 7 for i in range(61)], 24, 8),
+    ("600 children", [-1] + [0] * 600, [5] + [1 + i % 3 for i in range(600)], 8, 4),
+    ("130 rows, all regular but the ends", [-1], [130], 1032, 2),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("label,parent,seg_len,Cch,w", EDGES, ids=[c[0] for c in EDGES])
+def test_conv_run_edges(L, label, parent, seg_len, Cch, w, dtype):
+    from paper_2608_28158_amd.plan import HartsPlan
+    print(f"[gpu] conv {label} channels={Cch} w={w} {dtype}", flush=True)
+    plan = HartsPlan(parent, seg_len, 64)
+    Cn = int(np.sum(seg_len))
+    r = np.random.default_rng(Cn + w + Cch)
+    x = r.standard_normal((Cn, Cch)).astype(np.float32)
+    dy = r.standard_normal((Cn, Cch)).astype(np.float32)
+    W = r.standard_normal((Cch, w)).astype(np.float32)
+    if dtype == "bf16":
+        x, dy = to_bf16_roundtrip(x), to_bf16_roundtrip(dy)
+    phys = phys_index(seg_len, plan["seg_row"])
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def dev(a):
+        out = np.empty_like(a)
+        out[phys] = a
+        return torch.from_numpy(out).to("cuda", tdt).contiguous()
+
+    y, dx, dW = run_conv(L, plan, dev(x), W, dev(dy), w, tdt)
+    y_ref = conv_fwd(parent, seg_len, x, W)
+    dx_ref, dW_ref = conv_bwd(parent, seg_len, x, W, dy)
+    # dx sums up to 600 consumers in float32, dW up to 1,200 rows: far inside TOL
+    errs = {"y": max_rel(y.float().cpu().numpy()[phys], y_ref),
+            "dx": max_rel(dx.float().cpu().numpy()[phys], dx_ref),
+            "dW": max_rel(dW.cpu().numpy(), dW_ref)}
+    assert all(e <= TOL[dtype] for e in errs.values()), errs
+
+
 def test_conv_64k_workload_6144_channels_sampled(L):
     from paper_2608_28158_amd.plan import HartsPlan
     f, _, cfg = forest_for_config(2)
