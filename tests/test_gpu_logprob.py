@@ -186,3 +186,49 @@ def test_logp_invalid_indices_give_nan_not_a_fault(L):
     null = C.c_void_p()
     assert L.harts_logp_fwd(_lib.HARTS_BF16, Cn, 12, null, 0, null, null, null, null,
                             null) == _lib.HARTS_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("Cn,V", [(5, 8), (7, 8184), (7, 8192), (7, 16376), (7, 16384), (6, 40008), (34000, 2048),
+                                  (70000, 2048)])
+def test_logp_launch_edges(L, Cn, V, dtype):
+    """Rows just below and at the 2,048 vectors of the wide launch, logits on
+    both sides of the 256 MB of the non-temporal one; rows without a gradient
+    (no position, all masked, gradients that cancel over two targets, a row
+    with an infinite logit), more positions on one row than it has threads.
+    Reference: float64 log-softmax and the scatter of the gradients."""
+    r = np.random.default_rng(Cn + V)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    z = (torch.randn((Cn, V), device="cuda", generator=gen) * 2).to(tdt)
+    z[4, 3] = float("inf")
+    # rows 0: none, 1: masked, 2: 2,500 positions, 3 and later: one or two
+    m = np.concatenate([[1] * 3, [2] * 2500, np.repeat(np.arange(3, Cn), 2)]).astype(np.int32)
+    y = r.integers(0, min(V, 50), len(m)).astype(np.int32)
+    order = np.lexsort((y, m))
+    m, y = m[order], y[order]
+    g = r.standard_normal(len(m)).astype(np.float32)
+    g[m == 1] = 0
+    last = np.nonzero(m == Cn - 1)[0]
+    g[last[0]] = -g[last[1]] if len(last) == 2 else 0
+    off = np.concatenate([[0], np.cumsum(np.bincount(m, minlength=Cn))]).astype(np.int64)
+    logp, dz, row_g = run_logp(L, z, m, y, off, np.arange(len(m), dtype=np.int32), g)
+    zd = z.double()
+    lse = torch.logsumexp(zd, 1)
+    md, yd, gd = torch.from_numpy(m).cuda().long(), torch.from_numpy(y).cuda().long(), torch.from_numpy(g).cuda().double()
+    G = torch.zeros(Cn, dtype=torch.float64, device="cuda").index_add_(0, md, gd)
+    ref = -G[:, None] * torch.exp(zd - lse[:, None])
+    ref.view(-1).index_add_(0, md * V + yd, gd)
+    ok = torch.isfinite(lse)
+    assert int((~ok).sum()) == 1 and bool(torch.isnan(dz[4]).any())
+    # one rounding of each element, and the float32 sum of up to 2,500 gradients
+    tol = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    for c0 in range(0, Cn, 8192):
+        s = slice(c0, c0 + 8192)
+        d = (dz[s].double() - ref[s])[ok[s]].abs().max()
+        assert float(d) <= tol * float(ref[s][ok[s]].abs().max()), (c0, float(d))
+    assert np.allclose(row_g, G.cpu().numpy(), rtol=1e-5, atol=2e-4)
+    fine = ok[md].cpu().numpy()
+    assert np.abs(logp - (zd[md, yd] - lse[md]).cpu().numpy())[fine].max() < 1e-5
+    assert not dz[0].any() and not dz[1].any()
+    torch.cuda.empty_cache()
