@@ -182,3 +182,82 @@ def test_attn_64k_workload_sampled(L):
     print("[gpu] attn 64k workload: " + ", ".join(f"{k_}={v_:.2e}" for k_, v_ in errs.items()), flush=True)
     record("attn 68k x 16 heads of 128 (sampled)", "bf16", errs)
     assert all(e <= TOL["bf16"] for e in errs.values()), errs
+
+
+# Views whose lengths and ancestor counts lie around the kernels' steps (32 and
+# 64 rows), waves (16 and 32) and workgroups (64 and 128).
+EDGES = [
+    ("lengths around 16 and 32", [-1, 0, 0, 0, 0, 0], [15, 16, 17, 31, 32, 33]),
+    ("lengths around 64", [-1, 0, 0, 0, 1], [63, 64, 65, 1, 130]),
+    ("lengths around 128", [-1, 0, 0, 0], [129, 127, 128, 255]),
+    ("one row", [-1], [1]),
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("wide", [False, True], ids=["64-row workgroups", "128-row workgroups"])
+@pytest.mark.parametrize("label,parent,seg_len", EDGES, ids=[c[0] for c in EDGES])
+def test_attn_tile_edges(L, label, parent, seg_len, wide, d):
+    """Both workgroup sizes (128 rows from 512 (tile, head) pairs on) at the
+    edges of their tiles.  All heads share the inputs of the first two, so the
+    oracle runs on two; tolerance as for the small forests."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    plan = HartsPlan(parent, seg_len, 64)
+    lay = views_of(L, plan)[0]
+    H = 2 * (-(-512 // (2 * lay.n_qtiles))) if wide else 2
+    assert (lay.n_qtiles * H >= 512) == wide and (lay.n_kvtiles * H >= 512) == wide
+    Cn = int(np.sum(seg_len))
+    r = np.random.default_rng(Cn + d)
+    q, k, v, dO = (to_bf16_roundtrip(r.standard_normal((Cn, 2, d)).astype(np.float32)) for _ in range(4))
+    phys = phys_index(seg_len, plan["seg_row"])
+
+    def dev(a):
+        out = np.empty_like(a)
+        out[phys] = a
+        return torch.from_numpy(np.tile(out, (1, H // 2, 1))).to("cuda", torch.bfloat16).contiguous()
+
+    scale = d ** -0.5
+    got = run_attn(L, plan, dev(q), dev(k), dev(v), dev(dO), H, d, scale)
+    ref = forest_attention(parent, seg_len, q, k, v, scale, dO=dO)
+    for n in ("o", "dq", "dk", "dv"):
+        x = got[n].float().cpu().numpy()[phys]
+        for h in range(0, H, 2):
+            assert np.array_equal(x[:, h:h + 2], x[:, :2]), (n, h)
+        assert max_rel(x[:, :2], ref[n]) <= TOL["bf16"], n
+
+
+def test_attn_bwd_parts_by_themselves(L):
+    """dq alone (no key tiles) and dk, dv alone (no query tiles) are the same
+    as together: delta of every row is there for either."""
+    from paper_2608_28158_amd import _lib
+    from paper_2608_28158_amd.plan import HartsPlan
+    label, parent, seg_len = SMALL[1]
+    H, d = 3, 64
+    plan = HartsPlan(parent, seg_len, 64)
+    Cn = int(np.sum(seg_len))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v, dO = (torch.randn((Cn, H, d), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(4))
+    full = run_attn(L, plan, q, k, v, dO, H, d, d ** -0.5)
+    lay, views, kv_rows, qt, kt, off, ent = views_of(L, plan)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    vd, kr, qd, kd, od, ed = (dev(a) for a in (views, kv_rows, qt, kt, off, ent))
+    rows = kr.long()
+    kvk, kvv = k[rows].contiguous(), v[rows].contiguous()
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    new = lambda: torch.empty((lay.n_kv, H, d), dtype=torch.float32, device="cuda")
+    parts = []
+    for nq, nk in ((lay.n_qtiles, 0), (0, lay.n_kvtiles)):
+        delta = torch.full((Cn, H), float("nan"), device="cuda")
+        dq, dkv, dvv = torch.zeros_like(q), new(), new()
+        _lib.check(L.harts_attn_bwd(_p(vd), _p(qd), nq, _p(kd), nk, Cn, H, d, C.c_float(d ** -0.5), _p(q), _p(kvk),
+                                    _p(kvv), _p(full["o"]), _p(full["lse"]), _p(dO), _p(delta), _p(dq), _p(dkv),
+                                    _p(dvv), st), "harts_attn_bwd")
+        parts.append((dq, dkv, dvv, delta))
+    assert torch.equal(parts[0][0], full["dq"])
+    for src, name in ((parts[1][1], "dk"), (parts[1][2], "dv")):
+        out = torch.empty_like(q)
+        _lib.check(L.harts_attn_scatter(_p(src), _p(od), _p(ed), Cn, lay.n_kv, H, d, _p(out), st), "scatter")
+        assert torch.equal(out, full[name]), name
+    ref = (full["o"].double() * dO.double()).sum(-1)
+    # float32 sum of 64 products of magnitude about 1
+    assert float((parts[1][3].double() - ref).abs().max()) < 1e-4
