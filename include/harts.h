@@ -163,7 +163,9 @@ int harts_plan_export(const harts_plan_t* plan, const harts_plan_arrays* dst);
  * runs one (block, head).  block_chunks is the largest of 64, 48, 32, 24,
  * 16, 12, 8 that still yields min_blocks blocks in the round (8 if none
  * does).  min_blocks = 0 chooses ceil(896 / H), i.e. about 896 (block, head)
- * workgroups per round; a plan fresh from harts_plan is set for H = 16.
+ * workgroups per round, and a round that 8-chunk blocks leave below that
+ * takes the smallest of 4, 2, 1 with at most 256 (block, head) workgroups
+ * (8 if none has); a plan fresh from harts_plan is set for H = 16.
  * Only the device descriptor image and the per-round block facts change:
  * fetch harts_plan_get_info / harts_plan_round_info / harts_plan_blob again
  * afterwards.  Results of the device calls do not depend on the blocking

@@ -620,33 +620,63 @@ __global__ __launch_bounds__(SCAN_THR) void k_fwd_blockscan(
   if (nb == 0) return;
   const float* s0 = init_state(is, li, H, h, SS4 * 4);
   float4 s = s0 ? reinterpret_cast<const float4*>(s0)[e4] : make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int bg = b0; bg < b0 + nb; bg += SCAN_PF) {
+  // a batch of summaries, with the bank entries and log-decays of its blocks
+  // (read in the chain, each of those cost it a memory latency)
+  const auto load = [&](float4& x, float& gm, int& eb, int bb) __attribute__((always_inline)) {
+    const int64_t bi = static_cast<int64_t>(bb) * H + h;
+    eb = blk_tab[bb * BLK_WORDS + BLK_END_BANK];
+    gm = gam[bi];
+    x = reinterpret_cast<const float4*>(dSb)[bi * SS4 + e4];
+  };
+  const auto step = [&](const float4& x, float gm, int eb, int bb) __attribute__((always_inline)) {
+    const int64_t bi = static_cast<int64_t>(bb) * H + h;
+    const float dec = __expf(gm);
+    s.x = dec * s.x + x.x;
+    s.y = dec * s.y + x.y;
+    s.z = dec * s.z + x.z;
+    s.w = dec * s.w + x.w;
+    reinterpret_cast<float4*>(S_end)[bi * SS4 + e4] = s;
+    if (eb >= 0 && bank) reinterpret_cast<float4*>(bank)[(static_cast<int64_t>(eb) * H + h) * SS4 + e4] = s;
+  };
+  // Whole batches: the next one is requested before this one's states are
+  // stored (loads and stores complete in order), past the last it again.  A
+  // chain of about 120 blocks took 43 us when every batch waited for the
+  // stores of the one before it and every block for its bank entry; now 15 us.
+  int bg = b0;
+  const int b_full = b0 + nb / SCAN_PF * SCAN_PF;
+  if (bg < b_full) {
     float4 x[SCAN_PF];
     float gm[SCAN_PF];
+    int eb[SCAN_PF];
 #pragma unroll
-    for (int i = 0; i < SCAN_PF; ++i) {
-      if (bg + i < b0 + nb) {
-        const int64_t bi = static_cast<int64_t>(bg + i) * H + h;
-        gm[i] = gam[bi];
-        x[i] = reinterpret_cast<const float4*>(dSb)[bi * SS4 + e4];
+    for (int i = 0; i < SCAN_PF; ++i) load(x[i], gm[i], eb[i], bg + i);
+    for (; bg < b_full; bg += SCAN_PF) {
+      float4 xn[SCAN_PF];
+      float gn[SCAN_PF];
+      int en[SCAN_PF];
+      const int nx = min(bg + SCAN_PF, b_full - SCAN_PF);
+#pragma unroll
+      for (int i = 0; i < SCAN_PF; ++i) load(xn[i], gn[i], en[i], nx + i);
+#pragma unroll
+      for (int i = 0; i < SCAN_PF; ++i) step(x[i], gm[i], eb[i], bg + i);
+#pragma unroll
+      for (int i = 0; i < SCAN_PF; ++i) {
+        x[i] = xn[i];
+        gm[i] = gn[i];
+        eb[i] = en[i];
       }
     }
+  }
+  {
+    float4 x[SCAN_PF - 1];
+    float gm[SCAN_PF - 1];
+    int eb[SCAN_PF - 1];
 #pragma unroll
-    for (int i = 0; i < SCAN_PF; ++i) {
-      const int b = bg + i;
-      if (b < b0 + nb) {
-        const int64_t bi = static_cast<int64_t>(b) * H + h;
-        const float dec = __expf(gm[i]);
-        s.x = dec * s.x + x[i].x;
-        s.y = dec * s.y + x[i].y;
-        s.z = dec * s.z + x[i].z;
-        s.w = dec * s.w + x[i].w;
-        reinterpret_cast<float4*>(S_end)[bi * SS4 + e4] = s;
-        const int eb = blk_tab[b * BLK_WORDS + BLK_END_BANK];
-        if (eb >= 0 && bank)
-          reinterpret_cast<float4*>(bank)[(static_cast<int64_t>(eb) * H + h) * SS4 + e4] = s;
-      }
-    }
+    for (int i = 0; i < SCAN_PF - 1; ++i)
+      if (bg + i < b0 + nb) load(x[i], gm[i], eb[i], bg + i);
+#pragma unroll
+    for (int i = 0; i < SCAN_PF - 1; ++i)
+      if (bg + i < b0 + nb) step(x[i], gm[i], eb[i], bg + i);
   }
   if (S_final && !skip1)
     reinterpret_cast<float4*>(S_final)[(static_cast<int64_t>(seq[SEQ_FINAL_LEAF]) * H + h) * SS4 + e4] = s;
@@ -685,42 +715,69 @@ __global__ __launch_bounds__(SCAN_THR) void k_bwd_blockscan(
   if (nb == 1) return;
   const float4* S4 = reinterpret_cast<const float4*>(S_end);
   float4 ds = reinterpret_cast<const float4*>(dS_final)[(static_cast<int64_t>(seq[SEQ_FINAL_LEAF]) * H + h) * SS4 + e4];
-  for (int bg = b0 + nb - 1; bg > b0; bg -= SCAN_PF) {
+  const auto load = [&](float4& u, float& gm, int& eb, int bb) __attribute__((always_inline)) {
+    const int64_t bi = static_cast<int64_t>(bb) * H + h;
+    eb = blk_tab[(bb - 1) * BLK_WORDS + BLK_END_BANK];
+    gm = gam[bi];
+    u = reinterpret_cast<const float4*>(U)[bi * SS4 + e4];
+  };
+  // ds: the adjoint at the end of block bb -> at its start = the end of bb - 1
+  const auto step = [&](const float4& u, float gm, int eb, int bb) __attribute__((always_inline)) {
+    const float dec = __expf(gm);
+    ds.x = dec * ds.x + u.x;
+    ds.y = dec * ds.y + u.y;
+    ds.z = dec * ds.z + u.z;
+    ds.w = dec * ds.w + u.w;
+    const int64_t pi = static_cast<int64_t>(bb - 1) * H + h;
+    float bsum = 0.f;
+    if (eb >= 0) {  // uniform over the workgroup
+      const float4 inj = reinterpret_cast<const float4*>(dbank)[(static_cast<int64_t>(eb) * H + h) * SS4 + e4];
+      const float4 s = S4[pi * SS4 + e4];
+      bsum = scan_block_sum(inj.x * s.x + inj.y * s.y + inj.z * s.z + inj.w * s.w, red, t);
+      ds.x += inj.x;
+      ds.y += inj.y;
+      ds.z += inj.z;
+      ds.w += inj.w;
+    }
+    if (t == 0) betap[pi * NSW + part] = bsum;
+    reinterpret_cast<float4*>(dS_end)[pi * SS4 + e4] = ds;
+  };
+  // blocks b0 + nb - 1 down to b0 + 1, in batches as in the forward
+  int bg = b0 + nb - 1;
+  const int b_full = bg - (nb - 1) / SCAN_PF * SCAN_PF;   // whole batches cover (b_full, bg]
+  if (bg > b_full) {
     float4 u[SCAN_PF];
     float gm[SCAN_PF];
+    int eb[SCAN_PF];
 #pragma unroll
-    for (int i = 0; i < SCAN_PF; ++i) {
-      if (bg - i > b0) {
-        const int64_t bi = static_cast<int64_t>(bg - i) * H + h;
-        gm[i] = gam[bi];
-        u[i] = reinterpret_cast<const float4*>(U)[bi * SS4 + e4];
+    for (int i = 0; i < SCAN_PF; ++i) load(u[i], gm[i], eb[i], bg - i);
+    for (; bg > b_full; bg -= SCAN_PF) {
+      float4 un[SCAN_PF];
+      float gn[SCAN_PF];
+      int en[SCAN_PF];
+      const int nx = max(bg - SCAN_PF, b_full + SCAN_PF);
+#pragma unroll
+      for (int i = 0; i < SCAN_PF; ++i) load(un[i], gn[i], en[i], nx - i);
+#pragma unroll
+      for (int i = 0; i < SCAN_PF; ++i) step(u[i], gm[i], eb[i], bg - i);
+#pragma unroll
+      for (int i = 0; i < SCAN_PF; ++i) {
+        u[i] = un[i];
+        gm[i] = gn[i];
+        eb[i] = en[i];
       }
     }
+  }
+  {
+    float4 u[SCAN_PF - 1];
+    float gm[SCAN_PF - 1];
+    int eb[SCAN_PF - 1];
 #pragma unroll
-    for (int i = 0; i < SCAN_PF; ++i) {
-      const int b = bg - i;
-      if (b <= b0) break;
-      // ds: the adjoint at the end of block b -> at its start = the end of b - 1
-      const float dec = __expf(gm[i]);
-      ds.x = dec * ds.x + u[i].x;
-      ds.y = dec * ds.y + u[i].y;
-      ds.z = dec * ds.z + u[i].z;
-      ds.w = dec * ds.w + u[i].w;
-      const int64_t pi = static_cast<int64_t>(b - 1) * H + h;
-      const int eb = blk_tab[(b - 1) * BLK_WORDS + BLK_END_BANK];
-      float bsum = 0.f;
-      if (eb >= 0) {  // uniform over the workgroup
-        const float4 inj = reinterpret_cast<const float4*>(dbank)[(static_cast<int64_t>(eb) * H + h) * SS4 + e4];
-        const float4 s = S4[pi * SS4 + e4];
-        bsum = scan_block_sum(inj.x * s.x + inj.y * s.y + inj.z * s.z + inj.w * s.w, red, t);
-        ds.x += inj.x;
-        ds.y += inj.y;
-        ds.z += inj.z;
-        ds.w += inj.w;
-      }
-      if (t == 0) betap[pi * NSW + part] = bsum;
-      reinterpret_cast<float4*>(dS_end)[pi * SS4 + e4] = ds;
-    }
+    for (int i = 0; i < SCAN_PF - 1; ++i)
+      if (bg - i > b0) load(u[i], gm[i], eb[i], bg - i);
+#pragma unroll
+    for (int i = 0; i < SCAN_PF - 1; ++i)
+      if (bg - i > b0) step(u[i], gm[i], eb[i], bg - i);
   }
 }
 
@@ -1503,11 +1560,13 @@ __global__ __launch_bounds__(SCAN_THR) void k_dg_carry(
   const int b_end = seq[SEQ_BLK_OFF] + seq[SEQ_N_BLK];
   float carry = 0.f;
   if (h < H) {
-    for (int bb = b; bb < b_end; ++bb) {
-      const int64_t bi = static_cast<int64_t>(bb) * H + h;
-      for (int p = part; p < NSW; p += NPART) carry += betap[bi * NSW + p];
-      if (bb > b && part == 0) carry += Rb[bi];
-    }
+    // the (block, term) pairs dealt over the parts, four requests in flight
+    const int n = (b_end - b) * NSW;
+#pragma unroll 4
+    for (int e = part; e < n; e += NPART)
+      carry += betap[(static_cast<int64_t>(b + e / NSW) * H + h) * NSW + e % NSW];
+#pragma unroll 4
+    for (int bb = b + 1 + part; bb < b_end; bb += NPART) carry += Rb[static_cast<int64_t>(bb) * H + h];
   }
   red[t] = carry;
   __syncthreads();

@@ -45,6 +45,17 @@ int32_t default_min_blocks(int32_t H) {
 
 namespace {
 
+// A round that cannot reach the target even with 8-chunk blocks takes 4, 2 or
+// 1 chunks per block, as few as keep its (block, head) workgroups within one
+// for each of the 256 CUs: its time is the chain of chunks of a block.  With
+// 8, 4, 2 and 1 chunks per block, forward + recompute + backward: 6,463 rows,
+// 4 heads of 128 (60 workgroups with 8): 320, 230, 200, 245 us; 3,476 rows, 4
+// heads of 64 (44): 213, 154, 132, 134 us; 26,519 rows, 3 heads of 64 (93):
+// 237, 187, 207, 280 us; but 12,140 rows, 16 heads of 64 (240): 250, 263, 300,
+// 410 us.  Within this bound the scratch of a round also stays below 32 MiB,
+// half of what harts_la_fwd_noalloc holds.
+constexpr int64_t kShortUnits = 256;
+
 struct Builder {
   int32_t n;
   int64_t B;
@@ -418,6 +429,13 @@ struct Builder {
       for (const int32_t cand : cands) {
         if (count_blocks(L, cand) >= min_blocks) { L.block_chunks = cand; break; }
       }
+      // a round too small for that takes shorter blocks still (kShortUnits)
+      if (p.short_heads > 0 && count_blocks(L, 8) < min_blocks) {
+        for (const int32_t cand : {4, 2, 1}) {
+          if (int64_t{count_blocks(L, cand)} * p.short_heads > kShortUnits) break;
+          L.block_chunks = cand;
+        }
+      }
       L.n_blk = count_blocks(L, L.block_chunks);
       L.seq_tab = off;
       off = align_up(off + int64_t(L.n_seq) * SEQ_WORDS);
@@ -563,17 +581,20 @@ extern "C" int harts_plan_set_blocks(harts_plan_t* p, int32_t H, int32_t min_blo
     return HARTS_EINVAL;
   }
   const int32_t target = min_blocks ? min_blocks : harts::default_min_blocks(H);
-  if (target == p->min_blocks) return HARTS_OK;
-  const int32_t old = p->min_blocks;
+  const int32_t short_heads = min_blocks ? 0 : H;
+  if (target == p->min_blocks && short_heads == p->short_heads) return HARTS_OK;
+  const int32_t old = p->min_blocks, old_heads = p->short_heads;
   try {
     harts::Builder bld;
     bld.n = p->n_seg;
     bld.B = p->chunk;
     bld.P = p;
     p->min_blocks = target;
+    p->short_heads = short_heads;
     bld.build_blob();
   } catch (const std::bad_alloc&) {
     p->min_blocks = old;
+    p->short_heads = old_heads;
     set_error("harts_plan_set_blocks: out of host memory (the plan's device tables are gone)");
     p->blob.clear();
     p->rounds.clear();
@@ -606,6 +627,7 @@ extern "C" int harts_plan(int32_t n_seg, const int32_t* parent, const int64_t* s
     p->n_seg = n_seg;
     p->chunk = chunk;
     p->min_blocks = harts::default_min_blocks(16);
+    p->short_heads = 16;
     if (!bld.children_and_positions()) { delete p; return HARTS_EINVAL; }
     bld.dynamic_program();
     if (!bld.recover() || !bld.finish()) { delete p; return HARTS_EINVAL; }

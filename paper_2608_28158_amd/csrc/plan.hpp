@@ -77,6 +77,7 @@ struct harts_plan_s {
   int32_t n_seg = 0, n_trees = 0, n_leaves = 0, K = 0, n_seq = 0, n_slots = 0;
   int32_t n_bank = 0, chunk = 0;
   int32_t min_blocks = 0;  // block target of the device tables (harts_plan_set_blocks)
+  int32_t short_heads = 0; // heads by which small rounds take blocks below 8 chunks (0: an explicit target, none do)
   int64_t C = 0, S = 0, R = 0, n_chunks = 0;
 
   std::vector<int32_t> parent;  // the forest as given (-1 marks a root)

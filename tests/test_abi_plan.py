@@ -220,3 +220,41 @@ def test_set_blocks_recuts_rounds_by_head_count(L):
     assert L.harts_plan_set_blocks(h, 16, -1) == _lib.HARTS_EINVAL
     assert L.harts_plan_set_blocks(None, 16, 0) == _lib.HARTS_EINVAL
     base.close()
+
+
+def test_small_rounds_take_short_blocks(L):
+    """A round that 8-chunk blocks leave below the default target takes the
+    smallest of 4, 2, 1 chunks with at most 256 (block, head) workgroups; an
+    explicit target never goes below 8; either way the blocks tile every
+    sequence, and recutting a plan gives what a fresh one has."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    long_tree = ([-1, 0, 0, 1, 1], [1500, 700, 90, 640, 333])
+    want = {}
+    for parent, seg_len in (long_tree, ([-1], [64 * 300]), ([-1] + [0] * 9, [130] + [70] * 9)):
+        for H in (1, 4, 16, 40):
+            p = HartsPlan(parent, seg_len, 64, heads=H)
+            wide = HartsPlan(parent, seg_len, 64, heads=H, min_blocks=100000)
+            for rd, rw in zip(p.rounds, wide.rounds):
+                c = rd["block_chunks"]
+                assert rw["block_chunks"] == 8
+                if rw["n_blk"] >= -(-896 // H):
+                    assert c >= 8
+                elif c < 8:
+                    assert rd["n_blk"] * H <= 256
+                else:
+                    assert c == 8 and rd["n_blk"] == rw["n_blk"]
+            for r, rd in enumerate(p.rounds):
+                tab = p.blob_host[rd["blk_tab_off"] // 4:][:rd["n_blk"] * 8].reshape(-1, 8)
+                seqs = p.blob_host[rd["seq_tab_off"] // 4:][:rd["n_seq"] * 16].reshape(-1, 16)
+                for s in range(rd["n_seq"]):
+                    mine = tab[tab[:, 0] == s]
+                    assert mine[0, 1] == 0 and np.array_equal(mine[1:, 1], np.cumsum(mine[:-1, 2]))
+                    assert mine[:, 2].sum() == seqs[s, 9] and mine[:, 2].max() <= rd["block_chunks"]
+            want[len(parent), H] = [rd["block_chunks"] for rd in p.rounds]
+            assert L.harts_plan_set_blocks(wide.handle, H, 0) == 0
+            blob = np.zeros_like(p.blob_host)
+            assert L.harts_plan_blob(wide.handle, blob.ctypes.data, blob.nbytes) == 0
+            assert np.array_equal(blob, p.blob_host)
+            p.close()
+            wide.close()
+    assert want[5, 1][0] == 1 and want[1, 4] == [8] and want[1, 1] == [2]

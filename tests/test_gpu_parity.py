@@ -239,3 +239,18 @@ def test_config2_recompute_bf16_sampled_heads():
 def test_config3_large_bf16_sampled_head():
     f, cfg, x = config_inputs(3)
     compare(f.parent, f.seg_len, x, cfg["H"], cfg["d"], "bf16", heads=[17], label="config3")
+
+
+@pytest.mark.parametrize("recompute", [False, True], ids=["saved", "recompute"])
+@pytest.mark.parametrize("dtype,d,H", [("f32", 64, 1), ("bf16", 128, 1), ("bf16", 64, 5)])
+def test_short_blocks_and_long_chains(dtype, d, H, recompute):
+    """Blocks of 1 and 2 chunks (the default for few heads): chains of up to
+    45 blocks through the scans, whole batches of eight and remainders, with
+    requested boundaries inside them; and a chain of exactly eight."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    parent, seg_len = [-1, 0, 0, 1, 1, -1], [1500, 700, 90, 640, 1333, 512]
+    plan = HartsPlan(parent, seg_len, 64, heads=H)
+    assert plan.rounds[0]["block_chunks"] == (1 if H == 1 else 2 if H == 5 else 8)
+    r = np.random.default_rng(d + H)
+    x = draw_inputs(int(np.sum(seg_len)), 4, H, d, d, r, dtype, n_trees=2, s0_scale=0.5)
+    compare(parent, seg_len, x, H, d, dtype, recompute=recompute, label=f"short blocks {dtype} d{d} H{H}")
