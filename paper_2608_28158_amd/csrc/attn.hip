@@ -41,6 +41,7 @@
 
 #include "harts.h"
 #include "la_common.hpp"
+#include "lds_load.hpp"
 #include "plan.hpp"
 
 namespace harts {
@@ -101,13 +102,9 @@ struct AtTile {
 };
 
 // Rows row0 .. row0 + NR - 1 (clamped to the first n) of head h of a
-// [rows, H, D] tensor, requested straight into an LDS tile (no registers, no
-// LDS write instructions).  The 16-byte pieces of a wave's request land in
-// consecutive LDS slots, so the lane picks the piece that belongs there.  The
-// tile is complete after this wave's vmcnt(0) and a barrier; it must lie in
-// the first 64 KB of the workgroup's LDS (16 bits of M0, which nothing else
-// in these kernels uses).  Written as asm because the compiler makes every LDS
-// read wait for such a load.
+// [rows, H, D] tensor, requested straight into an LDS tile (lds_load.hpp):
+// the 16-byte pieces of a wave's request land in consecutive LDS slots, so the
+// lane picks the piece that belongs there.
 template <int D>
 struct AtRequest {
   static constexpr int PPR = AtTile<D>::PPR;
@@ -123,14 +120,6 @@ struct AtRequest {
     p16 = 16 * ((slot % PPR) ^ AtTile<D>::swz(r0));   // (every request starts at a multiple of 16 rows)
     off = r0 * rowb + p16;
   }
-  __device__ static inline void issue(const void* base, uint32_t o, const bf16* dst) {
-    typedef __attribute__((address_space(3))) const bf16 lds_bf16;
-    const uint32_t d = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_bf16*)dst)));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(d), "v"(o), "s"(base)
-                 : "memory");
-  }
   template <int NR>
   __device__ inline void rows(const bf16* __restrict__ src, int64_t row0, int n, int h, const bf16* tile) const {
     static_assert(NR % RPE == 0 && RPE % 16 == 0, "whole requests");
@@ -138,24 +127,15 @@ struct AtRequest {
     if (n >= NR) {
 #pragma unroll
       for (int e = 0; e < NR / RPE; ++e)
-        issue(base + e * RPE * static_cast<int64_t>(rowb), off, tile + (e * AT_THR + 64 * w) * 8);
+        lds_load16(base + e * RPE * static_cast<int64_t>(rowb), off, tile + (e * AT_THR + 64 * w) * 8);
     } else {
 #pragma unroll
       for (int e = 0; e < NR / RPE; ++e)
-        issue(base, static_cast<uint32_t>(min(r0 + RPE * e, n - 1)) * rowb + p16,   // n < 128: below 2^31
+        lds_load16(base, static_cast<uint32_t>(min(r0 + RPE * e, n - 1)) * rowb + p16,   // n < 128: below 2^31
               tile + (e * AT_THR + 64 * w) * 8);
     }
   }
 };
-// Every request of this wave has landed (vmcnt 0; the builtin also tells the
-// compiler that no load of its own is out, or it would wait inside the loop
-// for registers loaded before it, and with them for the next requests); then
-// the workgroup meets.
-__device__ inline void at_landed() {
-  __builtin_amdgcn_s_waitcnt(0x0f70);
-  __syncthreads();
-}
-
 // The fragments of 16 rows of a [rows, H, D] tensor from row0 (rows clamped to
 // last), straight from global memory into registers.
 template <int D>
@@ -258,7 +238,7 @@ __global__ __launch_bounds__(AT_THR, NH == 2 ? 3 : 2) void k_attn_fwd(const int3
   }
   int buf = 0;
   for (int k0 = 0; k0 < kv_end; k0 += T, buf ^= 1) {
-    at_landed();                            // this step's tiles are here, the other pair's readers are done
+    lds_landed();                            // this step's tiles are here, the other pair's readers are done
     if (k0 + T < kv_end) {
       req.template rows<T>(kv_k, kvoff + k0 + T, kv_end - k0 - T, h, sT[buf ^ 1][0]);
       req.template rows<T>(kv_v, kvoff + k0 + T, kv_end - k0 - T, h, sT[buf ^ 1][1]);
@@ -456,7 +436,7 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
     for (int j = 0; j < NJ; ++j) acc[a][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   int buf = 0;
   for (int k0 = 0; k0 < kv_end; k0 += AT_T, buf ^= 1) {
-    at_landed();
+    lds_landed();
     if (k0 + AT_T < kv_end) {
       req.template rows<AT_T>(kv_k, kvoff + k0 + AT_T, kv_end - k0 - AT_T, h, sT[buf ^ 1][0]);
       req.template rows<AT_T>(kv_v, kvoff + k0 + AT_T, kv_end - k0 - AT_T, h, sT[buf ^ 1][1]);
@@ -604,7 +584,7 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dkdv(
   int buf = 0;
   for (int t0 = tq0; t0 < l; t0 += AT_TQ, buf ^= 1) {
     const int nq = min(AT_TQ, l - t0);
-    at_landed();
+    lds_landed();
     if (t0 + AT_TQ < l) {
       // (before the requests: the wait for pl must not become one for them)
       if (t < 2 * AT_TQ) sL[(buf ^ 1) * 2 * AT_TQ + t] = pl;

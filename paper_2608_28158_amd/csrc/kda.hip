@@ -38,12 +38,14 @@
 #include <string>
 
 #include "harts.h"
+#include "lds_load.hpp"
 #include "plan.hpp"
 
 namespace harts {
 namespace {
 
 typedef __bf16 bf16;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int KT = 512;   // threads per workgroup (8 waves: two per SIMD)
 constexpr int KB = 64;    // chunk rows
 
@@ -69,7 +71,21 @@ struct KdaGrads {
   void* dq; void* dk; void* dv;        // [C][H][d], the input dtype
   float* dg; float* dbeta;             // [C][H][d], [C][H]
   float* sdq; float* sdk; float* sdv; float* sdg; float* sdb;   // [n_slots][H][d], [n_slots][H]
+  int vec_dv;                          // dv and sdv allow four-element stores
 };
+
+// Four consecutive elements at p, by one store where vec says that p's
+// alignment allows it.
+template <typename T>
+__device__ inline void put4(T* p, const f32x4& x, int vec) {
+  const float y[4] = {x[0], x[1], x[2], x[3]};
+  if (vec) {
+    st4<T>(p, y);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) st<T>(p + e, y[e]);
+  }
+}
 
 // Per-(chunk, head) float32 blocks of the workspace (element offsets per
 // chunk-head given by D).
@@ -113,15 +129,15 @@ template <> struct RowVec<float> {
 // This thread's 16-byte pieces of the rows of one packed chunk and head
 // (zero for padding rows), held in registers from an early load to a later
 // store into LDS as float32 [64][LDS].
-template <typename T, int D>
+template <typename T, int D, int NT = KT>
 struct RowPre {
-  static constexpr int N = RowVec<T>::N, VR = D / N, NL = KB * VR / KT;
-  static_assert(NL >= 1 && NL * KT == KB * VR, "pieces per thread");
+  static constexpr int N = RowVec<T>::N, VR = D / N, NL = KB * VR / NT;
+  static_assert(NL >= 1 && NL * NT == KB * VR, "pieces per thread");
   uint4 u[NL];
   __device__ inline void load(const T* __restrict__ src, const int32_t* ent, int H, int h, int t) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int idx = t + i * KT, r = idx / VR, c = (idx % VR) * N;
+      const int idx = t + i * NT, r = idx / VR, c = (idx % VR) * N;
       const int32_t e = ent[r];
       u[i] = e >= 0 ? *reinterpret_cast<const uint4*>(src + (static_cast<int64_t>(e >> 1) * H + h) * D + c)
                     : make_uint4(0u, 0u, 0u, 0u);
@@ -131,47 +147,30 @@ struct RowPre {
   __device__ inline void store(float* s, int t) const {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int idx = t + i * KT, r = idx / VR, c = (idx % VR) * N;
+      const int idx = t + i * NT, r = idx / VR, c = (idx % VR) * N;
+      static_assert(LDS % 4 == 0, "16-byte pieces of the tile's rows");
       const uint32_t w[4] = {u[i].x, u[i].y, u[i].z, u[i].w};
-      float* d = s + r * LDS + c;
+      f32x4* d = reinterpret_cast<f32x4*>(s + r * LDS + c);
       if (N == 8) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          d[2 * e] = __uint_as_float(w[e] << 16);
-          d[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
-        }
+        for (int e = 0; e < 2; ++e)
+          d[e] = f32x4{__uint_as_float(w[2 * e] << 16), __uint_as_float(w[2 * e] & 0xffff0000u),
+                       __uint_as_float(w[2 * e + 1] << 16), __uint_as_float(w[2 * e + 1] & 0xffff0000u)};
       } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) d[e] = __uint_as_float(w[e]);
+        d[0] = f32x4{__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3])};
       }
     }
   }
 };
 
-template <typename T, int D, int LDS = D + 1>
-__device__ inline void load_rows(float* s, const T* __restrict__ src, const int32_t* ent, int H, int h, int t) {
-  constexpr int N = RowVec<T>::N, VR = D / N;
-  for (int idx = t; idx < KB * VR; idx += KT) {
-    const int r = idx / VR, c = (idx % VR) * N;
-    const int32_t e = ent[r];
-    float x[N];
-    if (e >= 0) RowVec<T>::get(src + (static_cast<int64_t>(e >> 1) * H + h) * D + c, x);
-    else
-#pragma unroll
-      for (int n = 0; n < N; ++n) x[n] = 0.f;
-#pragma unroll
-    for (int n = 0; n < N; ++n) s[r * LDS + c + n] = x[n];
-  }
-}
-
 // Cumulative sums along the 64 rows of every channel of s [64][LG], in
-// place: KT / D parts of KB / (KT / D) consecutive rows per channel, each
+// place: NT / D parts of KB / (NT / D) consecutive rows per channel, each
 // summed in registers, then offset by the totals of the parts before it
-// (sTot: KT floats).  Every thread calls it (it synchronises the workgroup).
-template <int D, int LG>
+// (sTot: NT floats).  Every thread calls it (it synchronises the workgroup).
+template <int D, int LG, int NT = KT>
 __device__ inline void cumsum_rows(float* s, float* sTot, int t) {
-  constexpr int NP = KT / D, RP = KB / NP;
-  static_assert(NP * D == KT && NP * RP == KB, "parts of the rows");
+  constexpr int NP = NT / D, RP = KB / NP;
+  static_assert(NP * D == NT && NP * RP == KB, "parts of the rows");
   const int d = t % D, part = t / D;
   float v[RP];
   float a = 0.f;
@@ -197,22 +196,21 @@ __device__ inline void load_decay(float* sG, float* sb, float* sTot, const float
   for (int idx = t; idx < KB * D / 4; idx += KT) {
     const int r = (4 * idx) / D, c = (4 * idx) % D;
     const int32_t e = ent[r];
-    float4 x = {0.f, 0.f, 0.f, 0.f};
-    if (e >= 0) x = *reinterpret_cast<const float4*>(g + (static_cast<int64_t>(e >> 1) * H + h) * D + c);
-    sG[r * LG + c] = x.x;
-    sG[r * LG + c + 1] = x.y;
-    sG[r * LG + c + 2] = x.z;
-    sG[r * LG + c + 3] = x.w;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (e >= 0) x = *reinterpret_cast<const f32x4*>(g + (static_cast<int64_t>(e >> 1) * H + h) * D + c);
+    *reinterpret_cast<f32x4*>(sG + r * LG + c) = x;
   }
   if (t < KB) sb[t] = ent[t] >= 0 ? beta[static_cast<int64_t>(ent[t] >> 1) * H + h] : 0.f;
   __syncthreads();
   cumsum_rows<D, LG>(sG, sTot, t);
 }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
 // C += A B for one 16 x 16 x 4 step: lane (k = lane / 16, i = lane % 16)
 // gives A[i][k] and B[k][i]; C's lane holds rows 4 (lane / 16) + r, column
-// lane % 16.
+// lane % 16.  With the operands exchanged it holds row lane % 16, columns
+// 4 (lane / 16) + r: one 16-byte store where the result goes to memory.
 __device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // The chunk's rows in four blocks of 16.  A pairwise decay between rows i
@@ -287,14 +285,15 @@ __device__ inline bool is_wide(const uint32_t* sWide, int I, int d) {
 // operands).  The in-block pairs of wide channels are summed exactly first
 // (4 x 4 tiles with the channels dealt over 16 adjacent lanes, summed by
 // lane exchanges) and added to the products.
-template <int D, int LD, int LT>
+template <int D, int LD, int LT, int NT>
 __device__ __forceinline__ void pair_sums(float* sA, float* __restrict__ gM, const float* sK, const float* sQ,
                                           const float* sG, float* sX, float* sF, uint32_t* sWide, int t) {
-  for (int p = t; p < KB * KB; p += KT) {
+  for (int p = 4 * t; p < KB * KB; p += 4 * NT) {
     const int i = p / KB, j = p % KB;
-    sA[i * LT + j] = 0.f;
-    sX[i * LT + j] = 0.f;
-    if (j > i) gM[p] = 0.f;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    *reinterpret_cast<f32x4*>(sA + i * LT + j) = z;
+    *reinterpret_cast<f32x4*>(sX + i * LT + j) = z;
+    if (j / PB > i / PB) *reinterpret_cast<f32x4*>(gM + p) = z;   // the blocks above the diagonal
   }
   if (t < 3 * D) {
     const int x = t / D, d = t % D;
@@ -308,7 +307,7 @@ __device__ __forceinline__ void pair_sums(float* sA, float* __restrict__ gM, con
     // the wide channels' in-block pairs, exact: tile (block, ti >= tj),
     // channels de, de + 16, .. (At into sA, M into sX)
     constexpr int NE = 16, DE = D / NE, NIT = 4 * 10 * NE;
-    for (int it = t; it < ((NIT + 63) / 64) * 64; it += KT) {
+    for (int it = t; it < ((NIT + 63) / 64) * 64; it += NT) {
       const bool live = it < NIT;
       const int tile = live ? it / NE : 0, de = it % NE;
       const int blk = tile / 10, tt = tile % 10;
@@ -374,7 +373,7 @@ __device__ __forceinline__ void pair_sums(float* sA, float* __restrict__ gM, con
   // to a finite value before its factor 0 applies.
   {
     const int lane = t & 63, li = lane & 15, lk = lane >> 4;
-    for (int o = t >> 6; o < 10; o += KT / 64) {
+    for (int o = t >> 6; o < 10; o += NT / 64) {
       int I, J;
       if (o < 4) I = J = o;
       else {
@@ -416,7 +415,7 @@ __device__ __forceinline__ void pair_sums(float* sA, float* __restrict__ gM, con
         const int i = PB * I + 4 * lk + r, j = PB * J + li;
         if (in) {
           if (j < i) sA[i * LT + j] += accA[r];
-          if (j <= i) gM[i * KB + j] = accM[r] + sX[i * LT + j];
+          gM[i * KB + j] = j <= i ? accM[r] + sX[i * LT + j] : 0.f;
         } else {
           sA[i * LT + j] = accA[r];
           gM[i * KB + j] = accM[r];
@@ -436,7 +435,7 @@ __device__ __forceinline__ void pair_sums(float* sA, float* __restrict__ gM, con
 // A block column needs only its own blocks and the diagonal ones, so the
 // waves proceed independently (their LDS writes and reads stay in program
 // order within the wave).
-template <int LT>
+template <int LT, int NT>
 __device__ inline void tri_inverse(float* sL, float* sW, const float* sA, const float* sb, int t) {
   constexpr int BS = 16;
   if (t < KB) {                                   // diagonal blocks, the column in registers
@@ -456,7 +455,7 @@ __device__ inline void tri_inverse(float* sL, float* sW, const float* sA, const 
 #pragma unroll
     for (int x = 0; x < BS; ++x) sL[(r0 + x) * LT + c] = col[x];
   } else {
-    for (int p = t - KB; p < KB * KB; p += KT - KB) {
+    for (int p = t - KB; p < KB * KB; p += NT - KB) {
       const int i = p / KB, j = p % KB;
       if (j / BS > i / BS) sL[i * LT + j] = 0.f;
     }
@@ -492,25 +491,25 @@ __device__ inline void tri_inverse(float* sL, float* sW, const float* sA, const 
 // LDS of the chunk preparation (floats): K and Q (row stride LD in the
 // pairwise sums, LW for the products with Tm, whose B operands run along k),
 // G, At (then Tm) and L^{-1} (stride LT), beta, channel factors of the block pairs, scan totals, wide flags.
-template <int D>
+template <int D, int NT>
 struct PrepLds {
   static constexpr int LD = D + 4, LW = D + 16, LT = KB + 4;
   static constexpr int K = 0, Q = K + KB * LW, G = Q + KB * LW, A = G + KB * LD, L = A + KB * LT, B = L + KB * LT,
-                       FAC = B + KB, TOT = FAC + 8 * D, WIDE = TOT + KT, ALL = WIDE + 4 * D / 32;
+                       FAC = B + KB, TOT = FAC + 8 * D, WIDE = TOT + NT, ALL = WIDE + 4 * D / 32;
 };
 
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(KT) void k_kda_prep(const int32_t* __restrict__ chunk_rows, int64_t c0, int H,
+template <typename T, int D, int NT>
+__global__ __launch_bounds__(NT) void k_kda_prep(const int32_t* __restrict__ chunk_rows, int64_t c0, int H,
                                                  const T* __restrict__ q, const T* __restrict__ k,
                                                  const T* __restrict__ v, const float* __restrict__ g,
                                                  const float* __restrict__ beta, float* __restrict__ ws) {
   using Y = WsLay<D>;
-  using P = PrepLds<D>;
-  constexpr int LD = P::LD, LW = P::LW, LT = P::LT, TDW = D / 32;
-  extern __shared__ float sm[];
+  using P = PrepLds<D, NT>;
+  constexpr int LD = P::LD, LW = P::LW, LT = P::LT, CB = 4 * (D / 16) / (NT / 64);   // column blocks of a wave in the last products
+  extern __shared__ __align__(16) float sm[];
   float* sK = sm + P::K;
   float* sQ = sm + P::Q;
   float* sG = sm + P::G;
@@ -526,8 +525,8 @@ __global__ __launch_bounds__(KT) void k_kda_prep(const int32_t* __restrict__ chu
   float* w = ws + (static_cast<int64_t>(c) * H + h) * Y::ALL;
   // k, q, g and v requested together at the start (k is stored twice, at
   // both strides; v waits in registers until the products with Tm)
-  RowPre<T, D> pk, pq, pv;
-  RowPre<float, D> pg;
+  RowPre<T, D, NT> pk, pq, pv;
+  RowPre<float, D, NT> pg;
   pk.load(k, ent, H, h, t);
   pq.load(q, ent, H, h, t);
   pg.load(g, ent, H, h, t);
@@ -537,58 +536,71 @@ __global__ __launch_bounds__(KT) void k_kda_prep(const int32_t* __restrict__ chu
   pq.template store<LD>(sQ, t);
   pg.template store<LD>(sG, t);
   __syncthreads();
-  cumsum_rows<D, LD>(sG, sTot, t);
+  cumsum_rows<D, LD, NT>(sG, sTot, t);
   // KB = K e^{G_B - G}, QG = Q e^G, gamma = e^{G_B} (before the pairwise
   // sums overwrite K and Q with their block factors)
-  for (int idx = t; idx < KB * D; idx += KT) {
+  for (int idx = 4 * t; idx < KB * D; idx += 4 * NT) {
     const int r = idx / D, d = idx % D;
-    const float G = sG[r * LD + d], GB = sG[(KB - 1) * LD + d];
-    w[Y::KBM + idx] = sK[r * LD + d] * __expf(GB - G);
-    w[Y::QG + idx] = sQ[r * LD + d] * __expf(G);
+    const f32x4 G = ld4(sG + r * LD + d), GB = ld4(sG + (KB - 1) * LD + d);
+    f32x4 x = ld4(sK + r * LD + d), y = ld4(sQ + r * LD + d);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[e] *= __expf(GB[e] - G[e]);
+      y[e] *= __expf(G[e]);
+    }
+    *reinterpret_cast<f32x4*>(w + Y::KBM + idx) = x;
+    *reinterpret_cast<f32x4*>(w + Y::QG + idx) = y;
   }
   if (t < D) w[Y::GAM + t] = __expf(sG[(KB - 1) * LD + t]);
   // At into sA and the workspace, M into the workspace
-  pair_sums<D, LD, LT>(sA, w + Y::M, sK, sQ, sG, sL, sFac, sWide, t);
+  pair_sums<D, LD, LT, NT>(sA, w + Y::M, sK, sQ, sG, sL, sFac, sWide, t);
   __syncthreads();
-  for (int p = t; p < KB * KB; p += KT) w[Y::AT + p] = sA[(p / KB) * LT + p % KB];
-  tri_inverse<LT>(sL, sQ, sA, sb, t);          // the Q tile is free now: scratch
-  for (int p = t; p < KB * KB; p += KT) w[Y::LINV + p] = sL[(p / KB) * LT + p % KB];
-  // Tm = L^{-1} Diag(beta) into sA; K e^G and V into the K and Q tiles (stride LW)
-  for (int p = t; p < KB * KB; p += KT) {
+  for (int p = 4 * t; p < KB * KB; p += 4 * NT)
+    *reinterpret_cast<f32x4*>(w + Y::AT + p) = ld4(sA + (p / KB) * LT + p % KB);
+  tri_inverse<LT, NT>(sL, sQ, sA, sb, t);          // the Q tile is free now: scratch
+  // L^{-1} (zero above the diagonal) to the workspace, Tm = L^{-1} Diag(beta)
+  // into sA; K e^G and V into the K and Q tiles (stride LW)
+  for (int p = 4 * t; p < KB * KB; p += 4 * NT) {
     const int i = p / KB, j = p % KB;
-    sA[i * LT + j] = j <= i ? sL[i * LT + j] * sb[j] : 0.f;
+    const f32x4 x = ld4(sL + i * LT + j);
+    *reinterpret_cast<f32x4*>(w + Y::LINV + p) = x;
+    *reinterpret_cast<f32x4*>(sA + i * LT + j) = x * ld4(sb + j);
   }
   pk.template store<LW>(sK, t);
   pv.template store<LW>(sQ, t);
   __syncthreads();
-  for (int idx = t; idx < KB * D; idx += KT) {
+  for (int idx = 4 * t; idx < KB * D; idx += 4 * NT) {
     const int r = idx / D, d = idx % D;
-    sK[r * LW + d] *= __expf(sG[r * LD + d]);
+    const f32x4 G = ld4(sG + r * LD + d);
+    f32x4 x = ld4(sK + r * LW + d);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] *= __expf(G[e]);
+    *reinterpret_cast<f32x4*>(sK + r * LW + d) = x;
   }
   __syncthreads();
-  // W = Tm (K e^G), U' = Tm V on float32 MFMA: wave w owns row block w / 2
-  // and column blocks (D / 32)(w % 2)..; Tm is zero above the diagonal
-  const int ti = wv >> 1, td0 = (wv & 1) * TDW;
-  f32x4 aW[TDW], aU[TDW];
+  // W = Tm (K e^G), U' = Tm V on float32 MFMA: a wave owns CB column blocks
+  // of one row block; Tm is zero above the diagonal
+  constexpr int WR = NT / 64 / 4;            // waves of a row block
+  const int ti = wv / WR, td0 = (wv % WR) * CB;
+  f32x4 aW[CB], aU[CB];
 #pragma unroll
-  for (int x = 0; x < TDW; ++x) aW[x] = aU[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int x = 0; x < CB; ++x) aW[x] = aU[x] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int s4 = 0; s4 < 4 * (ti + 1); ++s4) {
     const int kk = 4 * s4 + lk;
     const float a = sA[(16 * ti + li) * LT + kk];
 #pragma unroll
-    for (int x = 0; x < TDW; ++x) {
-      aW[x] = mfma4(a, sK[kk * LW + 16 * (td0 + x) + li], aW[x]);
-      aU[x] = mfma4(a, sQ[kk * LW + 16 * (td0 + x) + li], aU[x]);
+    for (int x = 0; x < CB; ++x) {
+      // (operands exchanged: a lane holds four columns of one row)
+      aW[x] = mfma4(sK[kk * LW + 16 * (td0 + x) + li], a, aW[x]);
+      aU[x] = mfma4(sQ[kk * LW + 16 * (td0 + x) + li], a, aU[x]);
     }
   }
 #pragma unroll
-  for (int x = 0; x < TDW; ++x)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int idx = (16 * ti + 4 * lk + r) * D + 16 * (td0 + x) + li;
-      w[Y::W + idx] = aW[x][r];
-      w[Y::UP + idx] = aU[x][r];
-    }
+  for (int x = 0; x < CB; ++x) {
+    const int idx = (16 * ti + li) * D + 16 * (td0 + x) + 4 * lk;
+    *reinterpret_cast<f32x4*>(w + Y::W + idx) = aW[x];
+    *reinterpret_cast<f32x4*>(w + Y::UP + idx) = aU[x];
+  }
 }
 
 // The state recurrence of one (sequence, head, SV state columns), chunk by
@@ -639,7 +651,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
   constexpr int64_t OA1 = REV ? Y::KBM : Y::W, OA2 = REV ? Y::W : Y::KBM, OP = REV ? Y::DXO : Y::UP;
   constexpr int64_t OSC = REV ? Y::DSN : Y::SC, OX = REV ? Y::DX : Y::X;
   constexpr float S1 = REV ? 1.f : -1.f, S2 = REV ? -1.f : 1.f;
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* sA1 = sm + L::A1;
   float* sA2 = sm + L::A2;
   float* sS = sm + L::S;
@@ -839,7 +851,7 @@ __global__ __launch_bounds__(KT) void k_kda_out(const int32_t* __restrict__ chun
                                                 float scale, const float* __restrict__ ws, T* __restrict__ o) {
   using Y = WsLay<D>;
   constexpr int VH = 64, NV = D / VH, LB = VH + 4;
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* sS = sm;                 // [D][68]
   float* sX = sS + D * LB;        // [64][68]
   const int b = blockIdx.x;
@@ -907,7 +919,7 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_prep(const int32_t* __restrict__
   using Y = WsLay<D>;
   constexpr int LD = D + 16, NT = D / 16, TS = NT * NT / (KT / 64), TX = 4 * NT / (KT / 64);
   static_assert(TS >= 1 && TX >= 1 && NT % TS == 0 && NT % TX == 0, "tiles of a wave share a row block");
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* sD = sm;                  // [64][D + 16]
   const int c = static_cast<int>(blockIdx.x / H + c0), h = blockIdx.x % H;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
@@ -934,7 +946,7 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_prep(const int32_t* __restrict__
       for (int n = 0; n < N; ++n) x[n] = 0.f;
       if (e >= 0 && (e & 1)) RowVec<T>::get(dO + (static_cast<int64_t>(e >> 1) * H + h) * D + cc, x);
 #pragma unroll
-      for (int n = 0; n < N; ++n) sD[r * LD + cc + n] = x[n];
+      for (int n = 0; n < N; n += 4) *reinterpret_cast<f32x4*>(sD + r * LD + cc + n) = f32x4{x[n], x[n + 1], x[n + 2], x[n + 3]};
     }
   }
   __syncthreads();
@@ -947,153 +959,181 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_prep(const int32_t* __restrict__
   for (int s4 = 0; s4 < KB / 4; ++s4) {
     const int k = 4 * s4 + lk;
 #pragma unroll
-    for (int x = 0; x < TS; ++x) aS[x] = mfma4(paq[s4], sD[k * LD + 16 * (tvs + x) + li], aS[x]);
+    for (int x = 0; x < TS; ++x) aS[x] = mfma4(sD[k * LD + 16 * (tvs + x) + li], paq[s4], aS[x]);
     if (s4 >= 4 * tj)
 #pragma unroll
-      for (int x = 0; x < TX; ++x) aX[x] = mfma4(pam[s4], sD[k * LD + 16 * (tvx + x) + li], aX[x]);
+      for (int x = 0; x < TX; ++x) aX[x] = mfma4(sD[k * LD + 16 * (tvx + x) + li], pam[s4], aX[x]);
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int x = 0; x < TS; ++x)
+    *reinterpret_cast<f32x4*>(w + Y::DSO + (16 * td + li) * D + 16 * (tvs + x) + 4 * lk) = scale * aS[x];
 #pragma unroll
-    for (int x = 0; x < TS; ++x) w[Y::DSO + (16 * td + 4 * lk + r) * D + 16 * (tvs + x) + li] = scale * aS[x][r];
-#pragma unroll
-    for (int x = 0; x < TX; ++x) w[Y::DXO + (16 * tj + 4 * lk + r) * D + 16 * (tvx + x) + li] = scale * aX[x][r];
-  }
+  for (int x = 0; x < TX; ++x)
+    *reinterpret_cast<f32x4*>(w + Y::DXO + (16 * tj + li) * D + 16 * (tvx + x) + 4 * lk) = scale * aX[x];
 }
 
 // Products of one (chunk, head) with its states, contracted over the value
 // index: dQG = scale dO S^T, dW = -dX S^T, dKB = X dSn^T, dgamma =
 // rowsum(dSn * S), dM = scale dO X^T (j <= i), dUV = dX V^T (j <= i).  On
-// float32 MFMA over slabs of PVS value columns staged in LDS: operands whose
-// rows run along the fragment's m coordinate (dO, dX, X) as [64][PVS + 4],
-// those whose rows run along k (S^T, dSn^T, X^T, V^T) transposed with
-// strides of 16 (mod 64 banks): every fragment read is conflict-free.  Wave
-// w owns row block w / 2 of the three 64 x D products (D / 32 column blocks
-// each) and the lower-triangle blocks of dM and dUV in that row block whose
-// column block has the parity of w.
+// float32 MFMA over slabs of PVS value columns, each slab loaded straight into
+// one of two LDS buffers while the one before it is used.  Every operand's
+// rows run along the fragment's m or n coordinate, so a lane reads 16 bytes
+// of its row and has its k for all four steps of the slab (k = 4 (lane / 16)
+// + step, alike on both sides).  Wave w owns row block w / 2 of the three
+// 64 x D products (D / 32 column blocks each) and the lower-triangle blocks
+// of dM and dUV in that row block whose column block has the parity of w.
+// What bounds it is the fp32 MFMA time (13.6 us a (chunk, head) at d = 128)
+// and 352 KB of workspace and row traffic (1,504 us for 17,888 of them: 4.2
+// TB/s).  Staged through registers and transposed into LDS, with the loads of
+// a slab in front of its products, it took 2,132 us.
 constexpr int PVS = 16;   // value columns per slab
-template <int D>
-struct ProdLds {
-  static constexpr int LA = PVS + 4, LS = D + 16, LJ = KB + 16;
-  static constexpr int O = 0, DX = O + KB * LA, XA = DX + KB * LA, S = XA + KB * LA, N = S + PVS * LS,
-                       XB = N + PVS * LS, V = XB + PVS * LJ, ALL = V + PVS * LJ;
+
+// Slab tiles: rows of 16 elements.  A float row is four 16-byte pieces, piece
+// p at slot p ^ swz(r): the lanes a 16-byte read takes together (see the
+// attention tiles: rows r of one set at piece p, of the other at p ^ 1, r and
+// r ^ 12 in the same set) then hit 16 different slots of the 64 banks.  A bf16
+// row is two pieces, read 8 bytes a lane.
+template <typename T> struct Slab;
+template <> struct Slab<float> {
+  static constexpr int PPR = 4;
+  __device__ static inline int swz(int r) { return (0x78 >> (2 * ((r >> 2) & 3))) & 3; }   // 0, 2, 3, 1
+  __device__ static inline f32x4 read(const float* t, int r, int lk) { return ld4(t + PVS * r + 4 * (lk ^ swz(r))); }
 };
+template <> struct Slab<bf16> {
+  static constexpr int PPR = 2;
+  __device__ static inline int swz(int r) { return (r >> 3) & 1; }
+  __device__ static inline f32x4 read(const bf16* t, int r, int lk) {
+    const uint2 u = *reinterpret_cast<const uint2*>(t + PVS * r + 8 * ((lk >> 1) ^ swz(r)) + 4 * (lk & 1));
+    return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                 __uint_as_float(u.y & 0xffff0000u)};
+  }
+};
+// One buffer (floats): S, dSn [D][16], dX, X [64][16], then dO and V [64][16] of T.
+template <typename T, int D>
+struct ProdLds {
+  static constexpr int RV = KB * PVS * static_cast<int>(sizeof(T)) / 4;
+  static constexpr int S = 0, N = S + D * PVS, DX = N + D * PVS, X = DX + KB * PVS, O = X + KB * PVS, V = O + RV,
+                       BUF = V + RV, ALL = 2 * BUF;
+  static_assert(ALL * 4 <= 65536, "loads into LDS reach 64 KB");
+};
+// rows that read as zero: padding (dO and V), replay rows (dO)
+__device__ __align__(16) uint4 kda_zero_piece[1] = {};  // never written
 
 template <typename T, int D>
 __global__ __launch_bounds__(KT, 4) void k_kda_bwd_prod(const int32_t* __restrict__ chunk_rows, int64_t c0, int H,
                                                      float scale, const T* __restrict__ v, const T* __restrict__ dO,
-                                                     float* __restrict__ ws) {
+                                                     int aligned, float* __restrict__ ws) {
   using Y = WsLay<D>;
-  using L = ProdLds<D>;
+  using L = ProdLds<T, D>;
+  using F = Slab<float>;
+  using R = Slab<T>;
   constexpr int TDW = D / 32;
-  extern __shared__ float sm[];
-  float* sO = sm + L::O;      // dO   [64][LA]
-  float* sDX = sm + L::DX;    // dX   [64][LA]
-  float* sXa = sm + L::XA;    // X    [64][LA]
-  float* sS = sm + L::S;      // S^T  [PVS][LS]
-  float* sN = sm + L::N;      // dSn^T
-  float* sXb = sm + L::XB;    // X^T  [PVS][LJ]
-  float* sV = sm + L::V;      // V^T
+  extern __shared__ __align__(16) float sm[];
   const int c = static_cast<int>(blockIdx.x / H + c0), h = blockIdx.x % H;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), li = lane & 15, lk = lane >> 4;
   const int32_t* ent = chunk_rows + static_cast<int64_t>(c) * KB;
   float* w = ws + (static_cast<int64_t>(c) * H + h) * Y::ALL;
   const int ti = wv >> 1, td0 = (wv & 1) * TDW;
-  const int32_t my_ent = ent[t % KB];     // the row this thread stages from dO and V
+  // What this lane loads of every slab: pieces of S and dSn (wave w: rows
+  // 16 w .., at d = 64 waves 4.. take dSn), of dX (waves 0..3) and X (4..7),
+  // and of a row of dO or V (own rows; own and replay rows).
+  constexpr int WPR = KB * R::PPR / 64;                 // waves a row tile takes (bf16: 2, float: 4)
+  const int r = 16 * (wv % (D / 16)) + lane / 4;        // S, dSn row
+  const uint32_t os = 4u * (D * r + 4 * ((lane & 3) ^ F::swz(r)));
+  const int rx = 16 * (wv & 3) + lane / 4;              // dX, X row
+  const uint32_t ox = 4u * ((wv < 4 ? Y::DX : Y::X) + D * rx + 4 * ((lane & 3) ^ F::swz(rx)));
+  const bool rows = wv < 2 * WPR, isv = wv >= WPR;
+  const int rr = (64 / R::PPR) * (wv % WPR) + lane / R::PPR, pr = (lane % R::PPR) ^ R::swz(rr);
+  const char* prow = reinterpret_cast<const char*>(kda_zero_piece);
+  uint32_t pstep = 0;                                   // bytes from slab to slab (0: the zero piece)
+  if (rows) {
+    const int32_t e = ent[rr];
+    if (e >= 0 && (isv || (e & 1))) {
+      prow = reinterpret_cast<const char*>((isv ? v : dO) + (static_cast<int64_t>(e >> 1) * H + h) * D) + 16 * pr;
+      pstep = PVS * sizeof(T);
+    }
+  }
+  const auto request = [&](int slab, float* b) __attribute__((always_inline)) {
+    const uint32_t dv = 4u * PVS * slab;
+    if (D == 128) {
+      lds_load16(w + Y::SC, os + dv, b + L::S + 256 * wv);
+      lds_load16(w + Y::DSN, os + dv, b + L::N + 256 * wv);
+    } else {
+      lds_load16(wv < 4 ? w + Y::SC : w + Y::DSN, os + dv, b + (wv < 4 ? L::S : L::N) + 256 * (wv & 3));
+    }
+    lds_load16(w, ox + dv, b + (wv < 4 ? L::DX : L::X) + 256 * (wv & 3));
+    if (rows) {
+      float* dst = b + (isv ? L::V : L::O) + 256 * (wv % WPR);
+      if (aligned) lds_load16(prow + slab * pstep, dst);
+      else *reinterpret_cast<uint4*>(dst + 4 * lane) = *reinterpret_cast<const uint4*>(prow + slab * pstep);
+    }
+  };
   f32x4 aQ[TDW], aW[TDW], aK[TDW], aM[2], aU[2];
 #pragma unroll
   for (int x = 0; x < TDW; ++x) aQ[x] = aW[x] = aK[x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int x = 0; x < 2; ++x) aM[x] = aU[x] = f32x4{0.f, 0.f, 0.f, 0.f};
   float aG = 0.f;
-  for (int v0 = 0; v0 < D; v0 += PVS) {
-    __syncthreads();
-    for (int idx = t; idx < D * PVS / 4; idx += KT) {       // consecutive lanes: consecutive rows d
-      const int d = idx % D, vq = (idx / D) * 4;
-      const f32x4 a = *reinterpret_cast<const f32x4*>(w + Y::SC + d * D + v0 + vq);
-      const f32x4 n = *reinterpret_cast<const f32x4*>(w + Y::DSN + d * D + v0 + vq);
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        sS[(vq + x) * L::LS + d] = a[x];
-        sN[(vq + x) * L::LS + d] = n[x];
-      }
-    }
-    for (int idx = t; idx < KB * PVS / 4; idx += KT) {
-      const int i = idx % KB, vq = (idx / KB) * 4;
-      const f32x4 a = *reinterpret_cast<const f32x4*>(w + Y::DX + i * D + v0 + vq);
-      const f32x4 x = *reinterpret_cast<const f32x4*>(w + Y::X + i * D + v0 + vq);
-      *reinterpret_cast<f32x4*>(sDX + i * L::LA + vq) = a;
-      *reinterpret_cast<f32x4*>(sXa + i * L::LA + vq) = x;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sXb[(vq + e) * L::LJ + i] = x[e];
-    }
-    {   // dO (own rows) and V, 16-byte loads (row i = t % 64 of every slab)
-      constexpr int N = RowVec<T>::N, VR = PVS / N;
-      static_assert(KB * VR <= KT, "one piece per thread");
-      if (t < KB * VR) {
-        const int i = t % KB, vv = (t / KB) * N;
-        const int32_t e = my_ent;
-        float xo[N], xv[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) xo[n] = xv[n] = 0.f;
-        if (e >= 0) {
-          const int64_t row = (static_cast<int64_t>(e >> 1) * H + h) * D + v0 + vv;
-          RowVec<T>::get(v + row, xv);
-          if (e & 1) RowVec<T>::get(dO + row, xo);
-        }
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-          sO[i * L::LA + vv + n] = xo[n];
-          sV[(vv + n) * L::LJ + i] = xv[n];
-        }
-      }
-    }
-    __syncthreads();
+  request(0, sm);
+  for (int slab = 0; slab < D / PVS; ++slab) {
+    const float* b = sm + (slab & 1) * L::BUF;
+    lds_landed();                                       // this slab is here, the other buffer is read no more
+    if (slab + 1 < D / PVS) request(slab + 1, sm + ((slab + 1) & 1) * L::BUF);
+    const T* bO = reinterpret_cast<const T*>(b + L::O);
+    const T* bV = reinterpret_cast<const T*>(b + L::V);
     if (t < D)
-#pragma unroll 4
-      for (int vv = 0; vv < PVS; ++vv) aG += sN[vv * L::LS + t] * sS[vv * L::LS + t];
 #pragma unroll
-    for (int s4 = 0; s4 < PVS / 4; ++s4) {
-      const int k = 4 * s4 + lk;
-      const float ao = sO[(16 * ti + li) * L::LA + k], adx = sDX[(16 * ti + li) * L::LA + k];
-      const float ax = sXa[(16 * ti + li) * L::LA + k];
-#pragma unroll
-      for (int x = 0; x < TDW; ++x) {
-        const float bs = sS[k * L::LS + 16 * (td0 + x) + li], bn = sN[k * L::LS + 16 * (td0 + x) + li];
-        aQ[x] = mfma4(ao, bs, aQ[x]);
-        aW[x] = mfma4(adx, bs, aW[x]);
-        aK[x] = mfma4(ax, bn, aK[x]);
+      for (int p = 0; p < 4; ++p) {
+        const f32x4 n4 = F::read(b + L::N, t, p), s4 = F::read(b + L::S, t, p);
+        aG += n4[0] * s4[0] + n4[1] * s4[1] + n4[2] * s4[2] + n4[3] * s4[3];
       }
+    // products with the operands exchanged: a lane ends with four columns of
+    // row 16 ti + li
+    const f32x4 ao = R::read(bO, 16 * ti + li, lk), adx = F::read(b + L::DX, 16 * ti + li, lk);
+    const f32x4 ax = F::read(b + L::X, 16 * ti + li, lk);
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const int tj = (wv & 1) + 2 * x;
-        if (tj <= ti) {
-          aM[x] = mfma4(ao, sXb[k * L::LJ + 16 * tj + li], aM[x]);
-          aU[x] = mfma4(adx, sV[k * L::LJ + 16 * tj + li], aU[x]);
+    for (int x = 0; x < TDW; ++x) {
+      const f32x4 bs = F::read(b + L::S, 16 * (td0 + x) + li, lk), bn = F::read(b + L::N, 16 * (td0 + x) + li, lk);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        aQ[x] = mfma4(bs[e], ao[e], aQ[x]);
+        aW[x] = mfma4(bs[e], adx[e], aW[x]);
+        aK[x] = mfma4(bn[e], ax[e], aK[x]);
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int tj = (wv & 1) + 2 * x;
+      if (tj <= ti) {
+        const f32x4 bx = F::read(b + L::X, 16 * tj + li, lk), bv = R::read(bV, 16 * tj + li, lk);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          aM[x] = mfma4(bx[e], ao[e], aM[x]);
+          aU[x] = mfma4(bv[e], adx[e], aU[x]);
         }
       }
     }
   }
 #pragma unroll
-  for (int x = 0; x < TDW; ++x)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int idx = (16 * ti + 4 * lk + r) * D + 16 * (td0 + x) + li;
-      w[Y::DQG + idx] = scale * aQ[x][r];
-      w[Y::DW + idx] = -aW[x][r];
-      w[Y::DKBM + idx] = aK[x][r];
-    }
+  for (int x = 0; x < TDW; ++x) {
+    const int idx = (16 * ti + li) * D + 16 * (td0 + x) + 4 * lk;
+    *reinterpret_cast<f32x4*>(w + Y::DQG + idx) = scale * aQ[x];
+    *reinterpret_cast<f32x4*>(w + Y::DW + idx) = -aW[x];
+    *reinterpret_cast<f32x4*>(w + Y::DKBM + idx) = aK[x];
+  }
   // dM and dUV: every tile of the row block is written (zeros above the diagonal)
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
-    const int tj = (wv & 1) + 2 * x;
+    const int tj = (wv & 1) + 2 * x, i = 16 * ti + li, j = 16 * tj + 4 * lk;
+    f32x4 m, u;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = 16 * ti + 4 * lk + r, j = 16 * tj + li;
-      const bool on = tj <= ti && j <= i;
-      w[Y::DM + i * KB + j] = on ? scale * aM[x][r] : 0.f;
-      w[Y::DUV + i * KB + j] = on ? aU[x][r] : 0.f;
+    for (int e = 0; e < 4; ++e) {
+      const bool on = tj <= ti && j + e <= i;
+      m[e] = on ? scale * aM[x][e] : 0.f;
+      u[e] = on ? aU[x][e] : 0.f;
     }
+    *reinterpret_cast<f32x4*>(w + Y::DM + i * KB + j) = m;
+    *reinterpret_cast<f32x4*>(w + Y::DUV + i * KB + j) = u;
   }
   if (t < D) w[Y::DGAM + t] = aG;
 }
@@ -1128,7 +1168,7 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_tm(const int32_t* __restrict__ c
   using L = BtmLds<D>;
   constexpr int SW = L::SW, NS = D / SW;
   static_assert(SW * KB / 4 == KT && (SW / 16) * 4 == KT / 64, "one float4 of a slab per thread; 2 column blocks x 4 row blocks per slab");
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* sG = sm + L::G;           // [64][LG] cumulative log-decay, then the slabs:
   float* sWa = sm + L::WA;         //   dW [64][LA]
   float* sWb = sm + L::WB;         //   dW [64][LB]
@@ -1165,9 +1205,13 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_tm(const int32_t* __restrict__ c
   load_decay<D, L::LG>(sG, sb, sTot, g, beta, ent, H, h, t);
   pk.template store<L::LK>(sKG, t);
   __syncthreads();
-  for (int idx = t; idx < KB * D; idx += KT) {
+  for (int idx = 4 * t; idx < KB * D; idx += 4 * KT) {
     const int r = idx / D, d = idx % D;
-    sKG[r * L::LK + d] *= __expf(sG[r * L::LG + d]);
+    const f32x4 G = ld4(sG + r * L::LG + d);
+    f32x4 x = ld4(sKG + r * L::LK + d);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] *= __expf(G[e]);
+    *reinterpret_cast<f32x4*>(sKG + r * L::LK + d) = x;
   }
   const float bj = sb[16 * wi + li];
   const int ns = KB / 4 - 4 * wi;                          // k steps of Tm^T products
@@ -1201,22 +1245,18 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_tm(const int32_t* __restrict__ c
       if (n < ns) {
         const int i = 4 * (4 * wi + n) + lk;
         const float a = pl[n] * bj;
-        aV = mfma4(a, sXb[i * L::LB + 16 * par + li], aV);
-        aK = mfma4(a, sWb[i * L::LB + 16 * par + li], aK);
+        aV = mfma4(sXb[i * L::LB + 16 * par + li], a, aV);   // (exchanged: the lane's row is 16 wi + li)
+        aK = mfma4(sWb[i * L::LB + 16 * par + li], a, aK);
       }
     }
-    const int col = SW * sl + 16 * par + li;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = 16 * wi + 4 * lk + r;
-      const int32_t e = sEnt[j];
-      if (e >= 0) {
-        const int32_t slt = sSlot[j];
-        if (slt < 0) st<T>(static_cast<T*>(go.dv) + (static_cast<int64_t>(e >> 1) * H + h) * D + col, aV[r]);
-        else go.sdv[(static_cast<int64_t>(slt) * H + h) * D + col] = aV[r];
-      }
-      w[Y::DKG + j * D + col] = aK[r];
+    const int col = SW * sl + 16 * par + 4 * lk, j = 16 * wi + li;
+    const int32_t e = sEnt[j];
+    if (e >= 0) {
+      const int32_t slt = sSlot[j];
+      if (slt < 0) put4<T>(static_cast<T*>(go.dv) + (static_cast<int64_t>(e >> 1) * H + h) * D + col, aV, go.vec_dv);
+      else put4<float>(go.sdv + (static_cast<int64_t>(slt) * H + h) * D + col, aV, go.vec_dv);
     }
+    *reinterpret_cast<f32x4*>(w + Y::DKG + j * D + col) = aK;
   }
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
@@ -1236,14 +1276,14 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_tm(const int32_t* __restrict__ c
 // cumulative sum of g.  Writes dq, dk, dg ([row][H][D]) and dbeta ([row][H])
 // of every real packed row: into the compact row's gradients when it is the
 // compact row's only packed row, else into its slot.
-template <typename T, int D>
-__global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict__ chunk_rows, int64_t c0, int H,
+template <typename T, int D, int NT>
+__global__ __launch_bounds__(NT) void k_kda_bwd_local(const int32_t* __restrict__ chunk_rows, int64_t c0, int H,
                                                       const T* __restrict__ q, const T* __restrict__ k,
                                                       const float* __restrict__ g, const float* __restrict__ beta,
                                                       float* __restrict__ ws, const KdaGrads go) {
   using Y = WsLay<D>;
   constexpr int LB = KB + 4;       // 64 x 64 tiles: a stride of 4 (mod 64 banks) for the MFMA fragment reads
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* sK = sm;                  // [64][D] k, later its block factors, then dG
   float* sQ = sK + KB * D;         // [64][D] q, later block factors, then the dG_B terms
   float* sG = sQ + KB * D;         // [64][D] cumulative log-decay
@@ -1253,8 +1293,8 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   float* sb = sY + KB * LB;        // [64] beta
   float* sdb = sb + KB;            // [64] dbeta
   float* sMid = sdb + KB;          // [3][D] middle factors
-  float* sTot = sMid + 3 * D;      // [2][KT] scan totals
-  uint32_t* sWide = reinterpret_cast<uint32_t*>(sTot + 2 * KT);   // [4 D / 32] wide flags
+  float* sTot = sMid + 3 * D;      // [2][NT] scan totals
+  uint32_t* sWide = reinterpret_cast<uint32_t*>(sTot + 2 * NT);   // [4 D / 32] wide flags
   int32_t* sEnt = reinterpret_cast<int32_t*>(sWide + 4 * D / 32);  // [64] row table entries
   int32_t* sSlot = sEnt + KB;                                        // [64] gradient slots
   const int c = static_cast<int>(blockIdx.x / H + c0), h = blockIdx.x % H;
@@ -1268,16 +1308,16 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   float* w = ws + (static_cast<int64_t>(c) * H + h) * Y::ALL;
   // every input tile requested at once: k, q, g, L^{-1} and dTm for now, At
   // and dM (held in registers) for the later phases
-  constexpr int NP = KB * KB / 4 / KT;                     // float4 of a 64 x 64 tile per thread
-  RowPre<T, D> pk, pq;
-  RowPre<float, D> pg;
+  constexpr int NP = KB * KB / 4 / NT;                     // float4 of a 64 x 64 tile per thread
+  RowPre<T, D, NT> pk, pq;
+  RowPre<float, D, NT> pg;
   f32x4 pL[NP], pT[NP], pA[NP], pM[NP];
   pk.load(k, ent, H, h, t);
   pq.load(q, ent, H, h, t);
   pg.load(g, ent, H, h, t);
 #pragma unroll
   for (int n = 0; n < NP; ++n) {
-    const int e = 4 * (t + KT * n);
+    const int e = 4 * (t + NT * n);
     pL[n] = *reinterpret_cast<const f32x4*>(w + Y::LINV + e);
     pT[n] = *reinterpret_cast<const f32x4*>(w + Y::DUV + e);
     pA[n] = *reinterpret_cast<const f32x4*>(w + Y::AT + e);
@@ -1286,7 +1326,7 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   const auto put64 = [&](float* dst, const f32x4* src) {
 #pragma unroll
     for (int n = 0; n < NP; ++n) {
-      const int e = 4 * (t + KT * n);
+      const int e = 4 * (t + NT * n);
       *reinterpret_cast<f32x4*>(dst + (e / KB) * LB + e % KB) = src[n];
     }
   };
@@ -1298,28 +1338,34 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   put64(sL, pL);
   put64(sT, pT);                                           // dTm
   __syncthreads();
-  cumsum_rows<D, D>(sG, sTot, t);                          // cumulative sums of g per channel
-  // dbeta_j from Tm = L^{-1} Diag(beta): sum_i dTm[i][j] L^{-1}[i][j]
-  if (t < KB) {
-    const int j = t;
-    float a = 0.f;
-    for (int i = j; i < KB; ++i) a += sT[i * LB + j] * sL[i * LB + j];
-    sdb[j] = a;
-  }
-  __syncthreads();
-  for (int p = t; p < KB * KB; p += KT) sT[(p / KB) * LB + p % KB] *= sb[p % KB];   // dLinv
-  __syncthreads();
-  // Y = dLinv L^{-T} (both factors lower triangular: Y[a][j] sums over
-  // b <= min(a, j)), on float32 MFMA, stored transposed (sY[j][a] = Y[a][j]).
-  // Wave w: row block w / 2, column blocks 2 (w % 2) and + 1.
+  cumsum_rows<D, D, NT>(sG, sTot, t);                          // cumulative sums of g per channel
+  // dbeta_j from Tm = L^{-1} Diag(beta): sum_i dTm[i][j] L^{-1}[i][j], the rows
+  // of a column dealt over LPJ neighbouring lanes
   {
-    const int lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4, ta = wv >> 1;
+    constexpr int LPJ = NT / KB;
+    const int j = t / LPJ;
+    float a = 0.f;
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      const int tj = 2 * (wv & 1) + x, ns = 4 * ((ta < tj ? ta : tj) + 1);
+    for (int n = 0; n < KB / LPJ; ++n) {
+      const int i = t % LPJ + LPJ * n;
+      a += sT[i * LB + j] * sL[i * LB + j];                // (both zero above the diagonal)
+    }
+#pragma unroll
+    for (int m = LPJ / 2; m >= 1; m >>= 1) a += __shfl_xor(a, m);
+    if (t % LPJ == 0) sdb[j] = a;
+  }
+  // Y = dLinv L^{-T} with dLinv = dTm Diag(beta) (both factors lower
+  // triangular: Y[a][j] sums over b <= min(a, j)), on float32 MFMA, stored transposed (sY[j][a] = Y[a][j]).
+  // The 16 blocks are dealt over the waves, neighbours in a row to one wave.
+  {
+    constexpr int BW = 16 / (NT / 64);       // blocks of a wave
+    const int lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4, ta = wv * BW / 4;
+#pragma unroll
+    for (int x = 0; x < BW; ++x) {
+      const int tj = wv * BW % 4 + x, ns = 4 * ((ta < tj ? ta : tj) + 1);
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
       for (int s4 = 0; s4 < ns; ++s4)
-        acc = mfma4(sT[(16 * ta + li) * LB + 4 * s4 + lk], sL[(16 * tj + li) * LB + 4 * s4 + lk], acc);
+        acc = mfma4(sT[(16 * ta + li) * LB + 4 * s4 + lk] * sb[4 * s4 + lk], sL[(16 * tj + li) * LB + 4 * s4 + lk], acc);
 #pragma unroll
       for (int r = 0; r < 4; ++r) sY[(16 * tj + li) * LB + 16 * ta + 4 * lk + r] = acc[r];
     }
@@ -1330,7 +1376,7 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   // sum_j dA_ij At_ij; dAt = beta_i dA
   {
     const int lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
-    for (int tb = wv; tb < 10; tb += KT / 64) {
+    for (int tb = wv; tb < 10; tb += NT / 64) {
       int ti = 0;
       while ((ti + 1) * (ti + 2) / 2 <= tb) ++ti;
       const int tj = tb - ti * (ti + 1) / 2;
@@ -1343,23 +1389,20 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
         sT[i * LB + j] = i > j ? -acc[r] : 0.f;
       }
     }
-    for (int p = t; p < KB * KB; p += KT) {        // the blocks above the diagonal
-      const int i = p / KB, j = p % KB;
-      if (j / 16 > i / 16) sT[i * LB + j] = 0.f;
-    }
-  }
+  }                                                        // (above the diagonal dTm's zeros are still there)
   __syncthreads();
-  put64(sY, pA);                                           // Y is done: At into its tile
-  __syncthreads();
-  if (t < KB) {
-    float a = 0.f;
-    for (int j = 0; j < t; ++j) a += sT[t * LB + j] * sY[t * LB + j];
-    sdb[t] += a;
-  }
-  __syncthreads();
-  for (int p = t; p < KB * KB; p += KT) {
-    const int i = p / KB, j = p % KB;
-    sT[i * LB + j] *= sb[i];                                // dAt
+  // dbeta_i += sum_j dA_ij At_ij, 16 lanes a row, At still in registers; then
+  // dAt = beta_i dA
+#pragma unroll
+  for (int n = 0; n < NP; ++n) {
+    const int e = 4 * (t + NT * n), i = e / KB, j = e % KB;
+    f32x4 x = ld4(sT + i * LB + j);
+    float a = x[0] * pA[n][0] + x[1] * pA[n][1] + x[2] * pA[n][2] + x[3] * pA[n][3];
+#pragma unroll
+    for (int m = 8; m >= 1; m >>= 1) a += __shfl_xor(a, m);
+    if ((t & 15) == 0) sdb[i] += a;
+    x *= sb[i];
+    *reinterpret_cast<f32x4*>(sT + i * LB + j) = x;
   }
   put64(sL, pM);                                           // dM
   __syncthreads();
@@ -1379,12 +1422,11 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   // in-block pairs of wide channels are summed exactly first, one tile of
   // TRW rows x 4 channels per thread, which then takes the elementwise terms.
   {
-    constexpr int TRW = KB * (D / 4) / KT;   // rows per thread tile
+    constexpr int TRW = KB * (D / 4) / NT;   // rows per thread tile
     constexpr int NCT = D / 4;               // channel tiles
-    static_assert(TRW >= 1 && (KB / TRW) * NCT == KT && PB % TRW == 0, "one tile per thread");
+    static_assert(TRW >= 1 && (KB / TRW) * NCT == NT && PB % TRW == 0, "one tile per thread");
     const int i0 = (t / NCT) * TRW, d0 = (t % NCT) * 4, I = i0 / PB;
     float kr[TRW][4], qr[TRW][4];
-    float rd1[TRW][4], rd2[TRW][4], cd[TRW][4];
     const auto f4 = [](const float* p, float* x) {
       const float4 u = *reinterpret_cast<const float4*>(p);
       x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
@@ -1393,17 +1435,24 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
     for (int r = 0; r < TRW; ++r) {
       f4(sK + (i0 + r) * D + d0, kr[r]);
       f4(sQ + (i0 + r) * D + d0, qr[r]);
-#pragma unroll
-      for (int cc = 0; cc < 4; ++cc) rd1[r][cc] = rd2[r][cc] = cd[r][cc] = 0.f;
     }
     if (t < 3 * D) {
       const int x = t / D, d = t % D;
       const int ri = x == 0 ? 2 * PB : 3 * PB, rj = x == 2 ? 2 * PB : PB;
       sMid[t] = __expf(sG[ri * D + d] - sG[rj * D + d]);
     }
-    if (wide_flags<D, D>(sWide, sG, t)) {
+    const bool any_wide = wide_flags<D, D>(sWide, sG, t);
+    if (any_wide) {
       // inside the block, exact for the wide channels: rows i0.. with
-      // columns j <= i, then the own rows as columns j with rows i >= j
+      // columns j <= i, then the own rows as columns j with rows i >= j.
+      // The sums wait in blocks of the workspace that the backward has read
+      // for the last time (dW, dX, dXo), not in registers through the
+      // products.
+      float rd1[TRW][4], rd2[TRW][4], cd[TRW][4];
+#pragma unroll
+      for (int r = 0; r < TRW; ++r)
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) rd1[r][cc] = rd2[r][cc] = cd[r][cc] = 0.f;
       float wm[4];
 #pragma unroll
       for (int cc = 0; cc < 4; ++cc) wm[cc] = is_wide<D>(sWide, I, d0 + cc) ? 1.f : 0.f;
@@ -1440,13 +1489,22 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
             cd[r][cc] += wm[cc] * __expf(fminf(gi[cc] - gr[r][cc], 0.f)) * (a * ki[cc] + m * qi[cc]);
         }
       }
+#pragma unroll
+      for (int r = 0; r < TRW; ++r) {
+        st4<float>(w + Y::DW + (i0 + r) * D + d0, rd1[r]);
+        st4<float>(w + Y::DX + (i0 + r) * D + d0, rd2[r]);
+        st4<float>(w + Y::DXO + (i0 + r) * D + d0, cd[r]);
+      }
     }
     const int lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
     constexpr int NT16 = D / 16;
-    static_assert(NT16 == KT / 64 || 2 * NT16 == KT / 64, "one or both kinds of terms per wave");
-    const bool doR = NT16 == KT / 64 || wv < NT16, doC = NT16 == KT / 64 || wv >= NT16;
+    static_assert(NT16 == NT / 64 || 2 * NT16 == NT / 64, "one or both kinds of terms per wave");
+    const bool doR = NT16 == NT / 64 || wv < NT16, doC = NT16 == NT / 64 || wv >= NT16;
     const int d = 16 * (wv % NT16) + li;
-    f32x4 r1v[4], r2v[4], cv[4];
+    // a wave with one kind of terms keeps them in the same registers
+    constexpr bool ONE = 2 * NT16 == NT / 64;
+    f32x4 r1v[4], r2v[4], cvx[ONE ? 1 : 4];
+    f32x4* const cv = ONE ? r1v : cvx;
     if (doR) {
 #pragma unroll
       for (int Ib = 0; Ib < 4; ++Ib) {
@@ -1521,14 +1579,6 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
         }
       }
     }
-    // the workspace terms of the elementwise phase, requested before the terms go through LDS
-    f32x4 wq[TRW], wk[TRW], wb[TRW];
-#pragma unroll
-    for (int r = 0; r < TRW; ++r) {
-      wq[r] = *reinterpret_cast<const f32x4*>(w + Y::DQG + (i0 + r) * D + d0);
-      wk[r] = *reinterpret_cast<const f32x4*>(w + Y::DKG + (i0 + r) * D + d0);
-      wb[r] = *reinterpret_cast<const f32x4*>(w + Y::DKBM + (i0 + r) * D + d0);
-    }
     float gb[4];
     f4(sG + (KB - 1) * D + d0, gb);
     __syncthreads();     // K, Q, dM and dAt are read no more: R1 into sK, R2 into sQ, C1 over the dM tiles
@@ -1549,6 +1599,14 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
 #pragma unroll
         for (int r = 0; r < 4; ++r) sC[(PB * Jb + 4 * lk + r) * D + d] = cv[Jb][r];
     }
+    // the workspace terms of the elementwise phase, requested as the terms go through LDS
+    f32x4 wq[TRW], wk[TRW], wb[TRW];
+#pragma unroll
+    for (int r = 0; r < TRW; ++r) {
+      wq[r] = *reinterpret_cast<const f32x4*>(w + Y::DQG + (i0 + r) * D + d0);
+      wk[r] = *reinterpret_cast<const f32x4*>(w + Y::DKG + (i0 + r) * D + d0);
+      wb[r] = *reinterpret_cast<const f32x4*>(w + Y::DKBM + (i0 + r) * D + d0);
+    }
     __syncthreads();
     // the elementwise terms of the own tile (dG into sK, the dG_B terms into sQ)
 #pragma unroll
@@ -1562,10 +1620,22 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
       f4(sQ + i * D + d0, R2);
       f4(sC + i * D + d0, C1);
       f4(sG + i * D + d0, gi);
+      if (any_wide) {
+        float u1[4], u2[4], u3[4];
+        f4(w + Y::DW + i * D + d0, u1);
+        f4(w + Y::DX + i * D + d0, u2);
+        f4(w + Y::DXO + i * D + d0, u3);
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) {
+          R1[cc] += u1[cc];
+          R2[cc] += u2[cc];
+          C1[cc] += u3[cc];
+        }
+      }
 #pragma unroll
       for (int cc = 0; cc < 4; ++cc) {
         const float G = gi[cc];
-        const float r1 = rd1[r][cc] + R1[cc], r2 = rd2[r][cc] + R2[cc], c1 = cd[r][cc] + C1[cc];
+        const float r1 = R1[cc], r2 = R2[cc], c1 = C1[cc];
         const float eG = __expf(G), eB = __expf(gb[cc] - G), k_ = kr[r][cc], q_ = qr[r][cc];
         dq[cc] = r1 + dqg[cc] * eG;
         dk[cc] = r2 + c1 + dkg[cc] * eG + dkb[cc] * eB;
@@ -1589,10 +1659,10 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
   }
   __syncthreads();
   // dG_B (gamma and the KB terms) and the reverse cumulative sum of dG, per
-  // channel: KT / D parts of consecutive rows, summed in registers, then
+  // channel: NT / D parts of consecutive rows, summed in registers, then
   // offset by dG_B and the totals of the later parts
   {
-    constexpr int NP = KT / D, RP = KB / NP;
+    constexpr int NP = NT / D, RP = KB / NP;
     const int d = t % D, part = t / D;
     float suf[RP];
     float a = 0.f, xs = 0.f;
@@ -1603,10 +1673,10 @@ __global__ __launch_bounds__(KT) void k_kda_bwd_local(const int32_t* __restrict_
       xs += sQ[(part * RP + r) * D + d];
     }
     sTot[part * D + d] = a;
-    sTot[KT + part * D + d] = xs;
+    sTot[NT + part * D + d] = xs;
     __syncthreads();
     float off = dgam * __expf(sG[(KB - 1) * D + d]);
-    for (int p = 0; p < NP; ++p) off += sTot[KT + p * D + d] + (p > part ? sTot[p * D + d] : 0.f);
+    for (int p = 0; p < NP; ++p) off += sTot[NT + p * D + d] + (p > part ? sTot[p * D + d] : 0.f);
 #pragma unroll
     for (int r = 0; r < RP; ++r) {
       const int i = part * RP + r;
@@ -1678,20 +1748,29 @@ int kda_status(const char* where) {
   return HARTS_OK;
 }
 
+// Threads of the preparation and the chunk-local backward, whose LDS (149 and
+// 161 KB at d = 128) leaves room for one workgroup per CU: at d = 128 sixteen
+// waves, so that a phase's LDS and memory waits have three other waves of the
+// SIMD to hide behind.  Preparation 2,303 -> 1,720 us, chunk-local backward
+// 2,140 -> 1,966 us for 17,888 (chunk, head) pairs; then, with 16-byte LDS and
+// workspace accesses in their element-wise passes and the dbeta sums spread
+// over the workgroup, 1,549 and 1,793 us.
 template <int D>
-constexpr size_t lds_prep() { return PrepLds<D>::ALL * sizeof(float); }
+constexpr int wide_threads() { return D == 128 ? 1024 : KT; }
+template <int D>
+constexpr size_t lds_prep() { return PrepLds<D, wide_threads<D>()>::ALL * sizeof(float); }
 template <int D, int SV>
 constexpr size_t lds_seq() { return SeqLds<D, SV>::ALL * sizeof(float); }
 template <int D>
 constexpr size_t lds_out() { return (D + KB) * 68 * sizeof(float); }
 template <int D>
 constexpr size_t lds_bprep() { return KB * (D + 16) * sizeof(float); }
-template <int D>
-constexpr size_t lds_bprod() { return ProdLds<D>::ALL * sizeof(float); }
+template <typename T, int D>
+constexpr size_t lds_bprod() { return ProdLds<T, D>::ALL * sizeof(float); }
 template <int D>
 constexpr size_t lds_btm() { return BtmLds<D>::ALL * sizeof(float); }
 template <int D>
-constexpr size_t lds_blocal() { return (3 * KB * D + 3 * KB * (KB + 4) + 2 * KB + 3 * D + 2 * KT + 4 * D / 32 + 2 * KB) * sizeof(float); }
+constexpr size_t lds_blocal() { return (3 * KB * D + 3 * KB * (KB + 4) + 2 * KB + 3 * D + 2 * wide_threads<D>() + 4 * D / 32 + 2 * KB) * sizeof(float); }
 
 struct KdaArgs {
   const int32_t* chunk_rows;
@@ -1722,7 +1801,8 @@ int kda_fwd_impl(const KdaArgs& a, const void* q, const void* k, const void* v, 
   const auto* tk = static_cast<const T*>(k);
   const auto* tv = static_cast<const T*>(v);
   if (a.n_chunks > 0) {
-    hipLaunchKernelGGL((k_kda_prep<T, D>), dim3(static_cast<uint32_t>(a.n_chunks * a.H)), dim3(KT), lds_prep<D>(), s,
+    hipLaunchKernelGGL((k_kda_prep<T, D, wide_threads<D>()>), dim3(static_cast<uint32_t>(a.n_chunks * a.H)),
+                       dim3(wide_threads<D>()), lds_prep<D>(), s,
                        a.chunk_rows, a.c0, a.H, tq, tk, tv, g, beta, ws);
     if (int rc = kda_status("k_kda_prep")) return rc;
   }
@@ -1771,13 +1851,15 @@ int kda_bwd_impl(const KdaArgs& a, const void* q, const void* k, const void* v, 
     if (int rc = kda_status("k_kda_seq (reverse)")) return rc;
   }
   if (a.n_chunks > 0) {
-    hipLaunchKernelGGL((k_kda_bwd_prod<T, D>), dim3(gc), dim3(KT), lds_bprod<D>(), s, a.chunk_rows, a.c0, a.H,
-                       a.scale, tv, td, ws);
+    hipLaunchKernelGGL((k_kda_bwd_prod<T, D>), dim3(gc), dim3(KT), (lds_bprod<T, D>()), s, a.chunk_rows, a.c0, a.H,
+                       a.scale, tv, td, static_cast<int>(((reinterpret_cast<uintptr_t>(tv) | reinterpret_cast<uintptr_t>(td)) & 15) == 0),
+                       ws);
     if (int rc = kda_status("k_kda_bwd_prod")) return rc;
     hipLaunchKernelGGL((k_kda_bwd_tm<T, D>), dim3(gc), dim3(KT), lds_btm<D>(), s, a.chunk_rows, a.c0, a.H, tk, g,
                        beta, ws, go);
     if (int rc = kda_status("k_kda_bwd_tm")) return rc;
-    hipLaunchKernelGGL((k_kda_bwd_local<T, D>), dim3(gc), dim3(KT), lds_blocal<D>(), s, a.chunk_rows, a.c0, a.H,
+    hipLaunchKernelGGL((k_kda_bwd_local<T, D, wide_threads<D>()>), dim3(gc), dim3(wide_threads<D>()), lds_blocal<D>(),
+                       s, a.chunk_rows, a.c0, a.H,
                        tq, tk, g, beta, ws, go);
     if (int rc = kda_status("k_kda_bwd_local")) return rc;
   }
@@ -1797,8 +1879,8 @@ bool kda_set_lds() {
   // the kernels need more than the default 64 KiB of dynamic LDS
   static bool done = false;
   if (done) return true;
-  const void* fns[] = {reinterpret_cast<const void*>(&k_kda_prep<bf16, D>),
-                       reinterpret_cast<const void*>(&k_kda_prep<float, D>),
+  const void* fns[] = {reinterpret_cast<const void*>(&k_kda_prep<bf16, D, wide_threads<D>()>),
+                       reinterpret_cast<const void*>(&k_kda_prep<float, D, wide_threads<D>()>),
                        reinterpret_cast<const void*>(&k_kda_seq<D, false, 32>),
                        reinterpret_cast<const void*>(&k_kda_seq<D, true, 32>),
                        reinterpret_cast<const void*>(&k_kda_seq<D, false, 64>),
@@ -1811,8 +1893,8 @@ bool kda_set_lds() {
                        reinterpret_cast<const void*>(&k_kda_bwd_prod<float, D>),
                        reinterpret_cast<const void*>(&k_kda_bwd_tm<bf16, D>),
                        reinterpret_cast<const void*>(&k_kda_bwd_tm<float, D>),
-                       reinterpret_cast<const void*>(&k_kda_bwd_local<bf16, D>),
-                       reinterpret_cast<const void*>(&k_kda_bwd_local<float, D>)};
+                       reinterpret_cast<const void*>(&k_kda_bwd_local<bf16, D, wide_threads<D>()>),
+                       reinterpret_cast<const void*>(&k_kda_bwd_local<float, D, wide_threads<D>()>)};
   for (const void* f : fns)
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return false;
   done = true;
@@ -1887,7 +1969,8 @@ extern "C" int harts_kda_bwd(const int32_t* chunk_rows, const int32_t* seq_tab, 
     return HARTS_EHIP;
   }
   const KdaArgs a{chunk_rows, seq_tab, req_tab, c0, n_chunks, s0, n_seq, H, scale};
-  const KdaGrads go{pos_slot, dq, dk, dv, dg, dbeta, sdq, sdk, sdv, sdg, sdb};
+  const int vec_dv = al(dv) && (!sdv || al(sdv));
+  const KdaGrads go{pos_slot, dq, dk, dv, dg, dbeta, sdq, sdk, sdv, sdg, sdb, vec_dv};
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dtype == HARTS_BF16)
     return d == 128 ? kda_bwd_impl<bf16, 128>(a, q, k, v, g, beta, dO, dS_final, dbank, dS0_seq, ws, go, s)

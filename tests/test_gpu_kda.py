@@ -211,3 +211,55 @@ def test_kda_64k_workload_sampled():
     print("[gpu] kda 64k workload: " + ", ".join(f"{a}={b:.2e}" for a, b in errs.items()), flush=True)
     record("kda 68k x 16 heads of 128 (sampled)", "bf16", errs)
     assert all(e <= TOL["bf16"] for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_kda_backward_unaligned_rows(dtype):
+    """v, dO, dv and the dv slots one element off a 16-byte boundary (element
+    by element stores, row loads through registers): the same bits as aligned."""
+    import ctypes as C
+    from paper_2608_28158_amd import _lib
+    from paper_2608_28158_amd.kda import KdaRunner, _p
+    from paper_2608_28158_amd.plan import HartsPlan
+    label, parent, seg_len = CASES[2]
+    H, d = 2, 128
+    plan = HartsPlan(parent, seg_len, 64, heads=H)
+    Cn = int(np.sum(seg_len))
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v, g, beta, dO, S0, dSf = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in draw(
+        Cn, H, d, plan["n_trees"], plan["n_leaves"], 5, dtype == "bf16"))
+    q, k, v, dO = (t.to(tdt) for t in (q, k, v, dO))
+
+    def off(t):
+        return torch.cat([t.new_zeros(1), t.reshape(-1)])[1:].view(t.shape)
+
+    code = _lib.HARTS_BF16 if dtype == "bf16" else _lib.HARTS_F32
+    scale, outs = d ** -0.5, []
+    for shift in (lambda t: t, off):
+        run = KdaRunner(plan, H, d, tdt)
+        v_, dO_ = shift(v), shift(dO)
+        run.forward(q, k, v_, g, beta, S0, scale)
+        sz, st = run.sizes, run._stream()
+        dbank = torch.zeros((plan["n_bank"], H, d, d), device="cuda")
+        dS0 = torch.empty((sz.n_seq, H, d, d), device="cuda")
+        # (rows with slots are not written: NaN stays)
+        dq, dk, dg, dbeta = (torch.full_like(t, float("nan")) for t in (q, k, g, beta))
+        dv = shift(torch.full_like(v, float("nan")))
+        ns = max(sz.n_slots, 1)
+        sq, sk, sg = (torch.empty((ns, H, d), device="cuda") for _ in range(3))
+        sv, sb = shift(torch.empty((ns, H, d), device="cuda")), torch.empty((ns, H), device="cuda")
+        assert sz.n_slots > 0 and (dv.data_ptr() % 16 != 0) == (shift is off)
+        for s0, s1, c0, c1, g0, g1 in reversed(run.rounds):
+            _lib.check(run.L.harts_kda_bwd(
+                _p(run.d_rows), _p(run.d_seq), _p(run.d_req), _p(run.d_slot), c0, c1 - c0, s0, s1 - s0, code, H, d,
+                C.c_float(scale), _p(q), _p(k), _p(v_), _p(g), _p(beta), _p(dO_), _p(dSf), _p(dbank), _p(dS0),
+                _p(run.ws), _p(dq), _p(dk), _p(dv), _p(dg), _p(dbeta), _p(sq), _p(sk), _p(sv), _p(sg), _p(sb), st),
+                "harts_kda_bwd")
+            _lib.check(run.L.harts_kda_bank_add(_p(run.d_group), g0, g1 - g0, _p(run.d_gseq), H * d * d, _p(dS0),
+                                                _p(dbank), st), "harts_kda_bank_add")
+        torch.cuda.synchronize()
+        outs.append([t.clone() for t in (dq, dk, dg, dbeta, dbank)] + [dv.clone(), sv.clone()])
+    for n, (a, b) in enumerate(zip(*outs)):
+        assert torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), n
+    # rows replayed elsewhere go to the slots, all others to dv
+    assert int(torch.isnan(outs[0][5]).any(-1).any(-1).sum()) == sz.n_multi
