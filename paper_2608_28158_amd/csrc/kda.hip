@@ -13,7 +13,7 @@
 //   M[i][j] = sum_d q_i k_j e^{G_i - G_j} (j <= i),
 //   S_next = Diag(e^{G_B}) S + (K * e^{G_B - G})^T X.
 // Chunk-local quantities are formed in parallel (k_kda_prep); the state
-// recurrence runs per (sequence, head, slab of 32 or 64 state columns) over
+// recurrence runs per (sequence, head, slab of 16, 32 or 64 state columns) over
 // the chunks of the sequence (k_kda_seq); outputs again in parallel
 // (k_kda_out).  The backward mirrors it: dX and the state adjoints in
 // reverse chunk order (k_kda_seq, reverse), then every chunk-local gradient
@@ -626,28 +626,33 @@ __global__ __launch_bounds__(NT) void k_kda_prep(const int32_t* __restrict__ chu
 // fragment read hit 64 different banks.
 template <int D, int SV>
 struct SeqLds {
-  static constexpr int LA1 = D + 4, LA2 = D + 16, LS = SV + 4, LX = SV + 16;
+  static constexpr int LA1 = D + 4, LA2 = D + 16, LS = SV + 4, LX = SV == 16 ? 16 : SV + 16;
   static constexpr int A1 = 0, A2 = A1 + KB * LA1, S = A2 + KB * LA2, X = S + D * LS, G = X + KB * LX, ALL = G + D;
 };
 
-// Unroll counts of the state pass's two product loops: whole loops with
-// 32-column slabs, partial ones where the registers would not hold them.
+// Unroll counts of the state pass's two product loops: whole loops with 16-
+// and 32-column slabs, partial ones where the registers would not hold them.
 template <int D, int SV>
 struct SeqUnroll {
-  static constexpr int X = SV == 32 ? D / 16 : 2, S = SV == 32 ? KB / 4 : 4;
+  static constexpr int X = SV <= 32 ? D / 16 : 2, S = SV <= 32 ? KB / 4 : 4;
 };
+// Threads of the state pass: a 16-column slab has work for four waves.
+template <int SV>
+constexpr int seq_threads() { return SV == 16 ? 256 : KT; }
 
 template <int D, bool REV, int SV>
-__global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_tab, int32_t s0, int n_chain,
+__global__ __launch_bounds__(seq_threads<SV>()) void k_kda_seq(const int32_t* __restrict__ seq_tab, int32_t s0, int n_chain,
                                                 const int32_t* __restrict__ req_tab, int H, float* __restrict__ ws,
                                                 float* __restrict__ bank, float* __restrict__ S_final,
                                                 const float* __restrict__ dbank, float* __restrict__ dS0_seq) {
   using Y = WsLay<D>;
   using L = SeqLds<D, SV>;
-  constexpr int NV = D / SV, NW = KT / 64, TVN = SV / 16;
+  constexpr int NT = seq_threads<SV>(), NV = D / SV, NW = NT / 64, TVN = SV / 16;
   constexpr int XT = 4 * TVN / NW, ST = (D / 16) * TVN / NW;   // X and Sc tiles per wave
-  static_assert(XT >= 1 && ST >= 1 && TVN % XT == 0 && TVN % ST == 0, "tiles of a wave share their row block");
-  constexpr int NA = KB * D / 4 / KT;                          // float4 of one A tile per thread
+  static_assert(XT >= 1 && ST >= 1 && TVN % XT == 0 && (TVN % ST == 0 || TVN == 1),
+                "a wave's tiles lie in one row block, or in consecutive ones of one column block");
+  constexpr bool SROWS = ST > TVN;                             // (the latter, for Sc)
+  constexpr int NA = KB * D / 4 / NT;                          // float4 of one A tile per thread
   constexpr int64_t OA1 = REV ? Y::KBM : Y::W, OA2 = REV ? Y::W : Y::KBM, OP = REV ? Y::DXO : Y::UP;
   constexpr int64_t OSC = REV ? Y::DSN : Y::SC, OX = REV ? Y::DX : Y::X;
   constexpr float S1 = REV ? 1.f : -1.f, S2 = REV ? -1.f : 1.f;
@@ -671,13 +676,15 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
   // this wave's tiles: Xc rows 16 xti.., columns 16 (xtv + x)..; Sc rows
   // 16 sti.., columns 16 (stv + x)..
   const int xti = (wv * XT) / TVN, xtv = (wv * XT) % TVN, sti = (wv * ST) / TVN, stv = (wv * ST) % TVN;
+  const auto srow = [&](int x) { return 16 * (sti + (SROWS ? x : 0)); };   // first row and column of Sc tile x
+  const auto scol = [&](int x) { return 16 * (stv + (SROWS ? 0 : x)); };
   auto slab_of = [&](const float* base, int64_t entry) { return base + (entry * H + h) * Y::DD + v0; };
   // running state into LDS, then into the accumulators
   if (!REV) {
     const float* src = slab_of(bank, init);
-    for (int idx = t; idx < D * SV; idx += KT) sS[(idx / SV) * L::LS + idx % SV] = src[(idx / SV) * D + idx % SV];
+    for (int idx = t; idx < D * SV; idx += NT) sS[(idx / SV) * L::LS + idx % SV] = src[(idx / SV) * D + idx % SV];
   } else {
-    for (int idx = t; idx < D * SV; idx += KT) {
+    for (int idx = t; idx < D * SV; idx += NT) {
       const int r = idx / SV, cc = idx % SV;
       float a = S_final ? slab_of(S_final, leaf)[r * D + cc] : 0.f;
       for (int q = 0; q < nr; ++q)
@@ -690,7 +697,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
 #pragma unroll
   for (int x = 0; x < ST; ++x)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) Sa[x][r] = sS[(16 * sti + 4 * lk + r) * L::LS + 16 * (stv + x) + li];
+    for (int r = 0; r < 4; ++r) Sa[x][r] = sS[(srow(x) + 4 * lk + r) * L::LS + scol(x) + li];
   // Register prefetch two chunks ahead in two sets (P and P2 in the
   // accumulator layout).  Every load is unconditional (past the sequence's
   // end its last chunk is requested again), so the count of outstanding
@@ -705,8 +712,8 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
     const float* w = ws + (static_cast<int64_t>(c_first + cc) * H + h) * Y::ALL;
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
-      pA1[Z][n] = *reinterpret_cast<const f32x4*>(w + OA1 + 4 * (t + KT * n));
-      pA2[Z][n] = *reinterpret_cast<const f32x4*>(w + OA2 + 4 * (t + KT * n));
+      pA1[Z][n] = *reinterpret_cast<const f32x4*>(w + OA1 + 4 * (t + NT * n));
+      pA2[Z][n] = *reinterpret_cast<const f32x4*>(w + OA2 + 4 * (t + NT * n));
     }
 #pragma unroll
     for (int x = 0; x < XT; ++x)
@@ -716,7 +723,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
     for (int x = 0; x < ST; ++x)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        pP2[Z][x][r] = REV ? w[Y::DSO + (16 * sti + 4 * lk + r) * D + v0 + 16 * (stv + x) + li] : 0.f;
+        pP2[Z][x][r] = REV ? w[Y::DSO + (srow(x) + 4 * lk + r) * D + v0 + scol(x) + li] : 0.f;
     pg[Z] = *reinterpret_cast<const f32x4*>(w + Y::GAM + 4 * (t % (D / 4)));
   };
   int rq = 0;
@@ -731,7 +738,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
     for (; rq < nr && req_tab[2 * (ro + rq)] <= cc; ++rq) {
       if (req_tab[2 * (ro + rq)] != cc) continue;
       float* dst = bank + (static_cast<int64_t>(req_tab[2 * (ro + rq) + 1]) * H + h) * Y::DD + v0;
-      for (int idx = t; idx < D * SV; idx += KT) dst[(idx / SV) * D + idx % SV] = sS[(idx / SV) * L::LS + idx % SV];
+      for (int idx = t; idx < D * SV; idx += NT) dst[(idx / SV) * D + idx % SV] = sS[(idx / SV) * L::LS + idx % SV];
     }
   };
   const auto chunk = [&](auto set, int step) __attribute__((always_inline)) {
@@ -742,7 +749,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
     // this chunk's operands into LDS, the running state to the workspace
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
-      const int e = 4 * (t + KT * n), r = e / D, c = e % D;
+      const int e = 4 * (t + NT * n), r = e / D, c = e % D;
       *reinterpret_cast<f32x4*>(sA1 + r * L::LA1 + c) = pA1[Z][n];
       *reinterpret_cast<f32x4*>(sA2 + r * L::LA2 + c) = pA2[Z][n];
     }
@@ -752,7 +759,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
     for (int x = 0; x < XT; ++x) acc[x] = f32x4{pP[Z][x][0], pP[Z][x][1], pP[Z][x][2], pP[Z][x][3]};
 #pragma unroll
     for (int x = 0; x < ST; ++x) sacc[x] = f32x4{pP2[Z][x][0], pP2[Z][x][1], pP2[Z][x][2], pP2[Z][x][3]};
-    for (int idx = t; idx < D * SV / 4; idx += KT) {
+    for (int idx = t; idx < D * SV / 4; idx += NT) {
       const int r = (4 * idx) / SV, c = (4 * idx) % SV;
       *reinterpret_cast<float4*>(w + OSC + r * D + v0 + c) = *reinterpret_cast<const float4*>(sS + r * L::LS + c);
     }
@@ -796,12 +803,18 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
 #pragma unroll
     for (int x = 0; x < ST; ++x)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sacc[x][r] += sg[16 * sti + 4 * lk + r] * Sa[x][r];
+      for (int r = 0; r < 4; ++r) sacc[x][r] += sg[srow(x) + 4 * lk + r] * Sa[x][r];
 #pragma unroll SeqUnroll<D, SV>::S
     for (int s = 0; s < KB / 4; ++s) {
-      const float a = S2 * sA2[(4 * s + lk) * L::LA2 + 16 * sti + li];
+      if constexpr (SROWS) {
+        const float b = sX[(4 * s + lk) * L::LX + scol(0) + li];
 #pragma unroll
-      for (int x = 0; x < ST; ++x) sacc[x] = mfma4(a, sX[(4 * s + lk) * L::LX + 16 * (stv + x) + li], sacc[x]);
+        for (int x = 0; x < ST; ++x) sacc[x] = mfma4(S2 * sA2[(4 * s + lk) * L::LA2 + srow(x) + li], b, sacc[x]);
+      } else {
+        const float a = S2 * sA2[(4 * s + lk) * L::LA2 + srow(0) + li];
+#pragma unroll
+        for (int x = 0; x < ST; ++x) sacc[x] = mfma4(a, sX[(4 * s + lk) * L::LX + scol(x) + li], sacc[x]);
+      }
     }
     if (REV)       // adjoints of the requested states at the start of chunk cc
       for (; rr >= 0 && req_tab[2 * (ro + rr)] >= cc; --rr)
@@ -810,13 +823,13 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
 #pragma unroll
           for (int x = 0; x < ST; ++x)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sacc[x][r] += db[(16 * sti + 4 * lk + r) * D + 16 * (stv + x) + li];
+            for (int r = 0; r < 4; ++r) sacc[x][r] += db[(srow(x) + 4 * lk + r) * D + scol(x) + li];
         }
 #pragma unroll
     for (int x = 0; x < ST; ++x) {
       Sa[x] = sacc[x];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sS[(16 * sti + 4 * lk + r) * L::LS + 16 * (stv + x) + li] = sacc[x][r];
+      for (int r = 0; r < 4; ++r) sS[(srow(x) + 4 * lk + r) * L::LS + scol(x) + li] = sacc[x][r];
     }
     __syncthreads();
   };
@@ -836,7 +849,7 @@ __global__ __launch_bounds__(KT) void k_kda_seq(const int32_t* __restrict__ seq_
   float* dst = REV ? dS0_seq + (static_cast<int64_t>(seq) * H + h) * Y::DD + v0
                    : (S_final ? S_final + (static_cast<int64_t>(leaf) * H + h) * Y::DD + v0 : nullptr);
   if (dst)
-    for (int idx = t; idx < D * SV; idx += KT) dst[(idx / SV) * D + idx % SV] = sS[(idx / SV) * L::LS + idx % SV];
+    for (int idx = t; idx < D * SV; idx += NT) dst[(idx / SV) * D + idx % SV] = sS[(idx / SV) * L::LS + idx % SV];
 }
 
 // Outputs of one (chunk, head, 64 state columns): O = scale (QG S + M X),
@@ -1782,17 +1795,37 @@ struct KdaArgs {
   float scale;
 };
 
-// The state pass is a chain over each sequence's chunks: with few
-// (sequence, head) chains, slabs of 32 state columns double the workgroups
-// (and halve each chain's work per chunk); with many, 64-column slabs read
-// each chunk's operands half as often.
+// State columns of a workgroup of the state pass, which is a chain over each
+// sequence's chunks: with few (sequence, head) chains, narrow slabs start more
+// workgroups and shorten each chain's work per chunk; with many, 64-column
+// slabs read each chunk's operands half as often.  16 columns as long as all
+// workgroups run at once: two of them fit a CU at d = 64 (48 KB of LDS), one
+// at d = 128 (85 KB).  Against 32 columns, forward and backward: 2,617 rows, 4
+// heads of 64: 355 -> 304 us; 6,463 rows, 4 heads of 128: 860 -> 763 us; 17,330
+// rows, 6 heads of 64 (312 to 624 workgroups): 1,102 -> 1,035 us.
 template <int D>
-bool seq_narrow(const KdaArgs& a) {
-  return static_cast<int64_t>(a.n_seq) * a.H * (D / 64) < 512;
+int seq_slab(const KdaArgs& a) {
+  const int64_t chains = static_cast<int64_t>(a.n_seq) * a.H;
+  return chains * (D / 16) <= (D == 64 ? 512 : 256) ? 16 : (chains * (D / 64) < 512 ? 32 : 64);
 }
 // Workgroups of the state pass: the chains rounded up to a multiple of 8,
 // times the slabs (see the id mapping in k_kda_seq).
 inline uint32_t seq_grid(int n_chain, int n_slab) { return static_cast<uint32_t>((n_chain + 7) / 8 * 8 * n_slab); }
+
+template <int D, bool REV>
+void launch_seq(const KdaArgs& a, float* ws, float* bank, float* S_final, const float* dbank, float* dS0_seq,
+                hipStream_t s) {
+  const int n_chain = a.n_seq * a.H;
+  const auto go = [&](auto kernel, int sv, int threads, size_t lds) {
+    hipLaunchKernelGGL(kernel, dim3(seq_grid(n_chain, D / sv)), dim3(threads), lds, s, a.seq_tab, a.s0, n_chain,
+                       a.req_tab, a.H, ws, bank, S_final, dbank, dS0_seq);
+  };
+  switch (seq_slab<D>(a)) {
+    case 16: go(k_kda_seq<D, REV, 16>, 16, seq_threads<16>(), lds_seq<D, 16>()); break;
+    case 32: go(k_kda_seq<D, REV, 32>, 32, seq_threads<32>(), lds_seq<D, 32>()); break;
+    default: go(k_kda_seq<D, REV, 64>, 64, seq_threads<64>(), lds_seq<D, 64>()); break;
+  }
+}
 
 template <typename T, int D>
 int kda_fwd_impl(const KdaArgs& a, const void* q, const void* k, const void* v, const float* g, const float* beta,
@@ -1807,13 +1840,7 @@ int kda_fwd_impl(const KdaArgs& a, const void* q, const void* k, const void* v, 
     if (int rc = kda_status("k_kda_prep")) return rc;
   }
   if (a.n_seq > 0) {
-    const int n_chain = a.n_seq * a.H;
-    if (seq_narrow<D>(a))
-      hipLaunchKernelGGL((k_kda_seq<D, false, 32>), dim3(seq_grid(n_chain, D / 32)), dim3(KT), (lds_seq<D, 32>()), s,
-                         a.seq_tab, a.s0, n_chain, a.req_tab, a.H, ws, bank, S_final, nullptr, nullptr);
-    else
-      hipLaunchKernelGGL((k_kda_seq<D, false, 64>), dim3(seq_grid(n_chain, D / 64)), dim3(KT), (lds_seq<D, 64>()), s,
-                         a.seq_tab, a.s0, n_chain, a.req_tab, a.H, ws, bank, S_final, nullptr, nullptr);
+    launch_seq<D, false>(a, ws, bank, S_final, nullptr, nullptr, s);
     if (int rc = kda_status("k_kda_seq")) return rc;
   }
   if (a.n_chunks > 0 && o) {
@@ -1839,15 +1866,7 @@ int kda_bwd_impl(const KdaArgs& a, const void* q, const void* k, const void* v, 
     if (int rc = kda_status("k_kda_bwd_prep")) return rc;
   }
   if (a.n_seq > 0) {
-    const int n_chain = a.n_seq * a.H;
-    if (seq_narrow<D>(a))
-      hipLaunchKernelGGL((k_kda_seq<D, true, 32>), dim3(seq_grid(n_chain, D / 32)), dim3(KT), (lds_seq<D, 32>()), s,
-                         a.seq_tab, a.s0, n_chain, a.req_tab, a.H, ws, nullptr, const_cast<float*>(dS_final), dbank,
-                         dS0_seq);
-    else
-      hipLaunchKernelGGL((k_kda_seq<D, true, 64>), dim3(seq_grid(n_chain, D / 64)), dim3(KT), (lds_seq<D, 64>()), s,
-                         a.seq_tab, a.s0, n_chain, a.req_tab, a.H, ws, nullptr, const_cast<float*>(dS_final), dbank,
-                         dS0_seq);
+    launch_seq<D, true>(a, ws, nullptr, const_cast<float*>(dS_final), dbank, dS0_seq, s);
     if (int rc = kda_status("k_kda_seq (reverse)")) return rc;
   }
   if (a.n_chunks > 0) {
@@ -1881,6 +1900,8 @@ bool kda_set_lds() {
   if (done) return true;
   const void* fns[] = {reinterpret_cast<const void*>(&k_kda_prep<bf16, D, wide_threads<D>()>),
                        reinterpret_cast<const void*>(&k_kda_prep<float, D, wide_threads<D>()>),
+                       reinterpret_cast<const void*>(&k_kda_seq<D, false, 16>),
+                       reinterpret_cast<const void*>(&k_kda_seq<D, true, 16>),
                        reinterpret_cast<const void*>(&k_kda_seq<D, false, 32>),
                        reinterpret_cast<const void*>(&k_kda_seq<D, true, 32>),
                        reinterpret_cast<const void*>(&k_kda_seq<D, false, 64>),

@@ -77,6 +77,15 @@ def test_kda_wide_state_slabs(dtype, d):
     assert max(s1 - s0 for s0, s1, *_ in run.rounds) * 32 * (d // 64) >= 512
 
 
+@pytest.mark.parametrize("dtype,d,H", [("f32", 64, 10), ("bf16", 128, 4)])
+def test_kda_middle_state_slabs(dtype, d, H):
+    """The star at head counts whose leaf round takes 32-column slabs: too many
+    chains for all 16-column workgroups to run at once, too few for 64."""
+    run = check_forest(*STAR, dtype, d, H)
+    chains = max(s1 - s0 for s0, s1, *_ in run.rounds) * H
+    assert chains * (d // 16) > (512 if d == 64 else 256) and chains * (d // 64) < 512
+
+
 # The edge-case forests of the linear-attention parity tests (forks on,
 # before and after chunk boundaries, replay across several ancestors, chains
 # of one-row segments, a star, two trees, exact chunk multiples).
