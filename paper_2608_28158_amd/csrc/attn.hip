@@ -48,7 +48,6 @@ namespace harts {
 namespace {
 
 constexpr int AT_THR = 256;          // 4 waves
-constexpr int AT_T = 64;             // keys of a dq step
 constexpr int AT_TQ = 32;            // queries of a step (dk/dv)
 constexpr int AT_WT = 128;           // rows of a table tile (queries in fwd/dq, keys in dk/dv)
 constexpr float AT_LOG2E = 1.4426950408889634f;
@@ -183,9 +182,11 @@ __device__ inline void at_block(int H, int& tile, int& sub, int& h) {
 // 16 NH of them (halves a).  Per step of T keys, every K fragment read from
 // LDS feeds all halves, and so does every V fragment.  The next step's tiles
 // are requested into the other pair of LDS tiles before this step computes.
-// 128-query workgroups take 32 keys a step: three of them fit a CU then, and
-// a step's softmax and LDS waits hide behind the products of two other waves
-// (the 64k call: 2,634 us against 2,870 with 64 keys and two workgroups).
+// 128-query workgroups of d = 128 take 32 keys a step: three of them fit a CU
+// then, and a step's softmax and LDS waits hide behind the products of two
+// other waves (the 64k call: 2,634 us against 2,870 with 64 keys and two
+// workgroups).  At d = 64 three fit with 64 keys too (30,000 rows, 16 heads:
+// 598 us with 32 keys, 574 with 64; four workgroups of either no faster).
 // 64-query ones, used where the chip is not full, take 64 (11.7 us against
 // 13.6 for 2,000 rows of 6 heads of 64).
 // ---------------------------------------------------------------------------
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(AT_THR, NH == 2 ? 3 : 2) void k_attn_fwd(const int3
   using R = AtRows<NH>;
   constexpr int NS = D / 32;  // 32-deep steps over d
   constexpr int NJ = D / 16;  // 16-column output tiles
-  constexpr int T = NH == 2 ? 32 : 64;   // keys of a step
+  constexpr int T = D == 128 && NH == 2 ? 32 : 64;   // keys of a step
   __shared__ __align__(16) bf16 sT[2][2][T * D];   // [buffer][K, V]
   int tile, sub, h;
   at_block<NH>(H, tile, sub, h);
@@ -377,7 +378,7 @@ __device__ inline void at_delta(int64_t e0, int64_t n, const bf16* __restrict__ 
 // the dk/dv kernel: as a kernel of their own (one thread an entry) they took
 // 215 us of an 11.8 ms backward and a launch of every small one.
 template <int D, int NH>
-__global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
+__global__ __launch_bounds__(AT_THR, D == 64 && NH == 2 ? 4 : 2) void k_attn_dq(
     const int32_t* __restrict__ views, const int32_t* __restrict__ qtiles, int H, float scale,
     const bf16* __restrict__ q, const bf16* __restrict__ kv_k, const bf16* __restrict__ kv_v,
     const bf16* __restrict__ o, const bf16* __restrict__ dO, const float* __restrict__ lse, uint32_t n_tile_wg,
@@ -386,7 +387,8 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
   using L = AtTile<D>;
   using R = AtRows<NH>;
   constexpr int NS = D / 32, NJ = D / 16;
-  __shared__ __align__(16) bf16 sT[2][2][AT_T * D];   // [buffer][K, V]
+  constexpr int T = D == 64 && NH == 2 ? 32 : 64;   // keys of a step
+  __shared__ __align__(16) bf16 sT[2][2][T * D];   // [buffer][K, V]
   if (blockIdx.x >= n_tile_wg) {
     at_delta<D>(static_cast<int64_t>(blockIdx.x - n_tile_wg) * AT_THR, n_rows, o, dO, delta);
     return;
@@ -403,8 +405,8 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
   if (nq <= 0) return;
   const int kv_end = hh + t0 + nq;
   const AtRequest<D> req(H, w, lane);
-  req.template rows<AT_T>(kv_k, kvoff, kv_end, h, sT[0][0]);
-  req.template rows<AT_T>(kv_v, kvoff, kv_end, h, sT[0][1]);
+  req.template rows<T>(kv_k, kvoff, kv_end, h, sT[0][0]);
+  req.template rows<T>(kv_v, kvoff, kv_end, h, sT[0][1]);
   const int i = lane & 15, g = lane >> 4;
   const int wq0 = t0 + R::WR * w;
   bf16x8 qf[NH][NS], df[NH][NS];
@@ -435,19 +437,19 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[a][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   int buf = 0;
-  for (int k0 = 0; k0 < kv_end; k0 += AT_T, buf ^= 1) {
+  for (int k0 = 0; k0 < kv_end; k0 += T, buf ^= 1) {
     lds_landed();
-    if (k0 + AT_T < kv_end) {
-      req.template rows<AT_T>(kv_k, kvoff + k0 + AT_T, kv_end - k0 - AT_T, h, sT[buf ^ 1][0]);
-      req.template rows<AT_T>(kv_v, kvoff + k0 + AT_T, kv_end - k0 - AT_T, h, sT[buf ^ 1][1]);
+    if (k0 + T < kv_end) {
+      req.template rows<T>(kv_k, kvoff + k0 + T, kv_end - k0 - T, h, sT[buf ^ 1][0]);
+      req.template rows<T>(kv_v, kvoff + k0 + T, kv_end - k0 - T, h, sT[buf ^ 1][1]);
     }
     if (!wave_live || k0 >= wave_end) continue;
     const bf16 *sK = sT[buf][0], *sV = sT[buf][1];
     // per 16-key group j: S and dP over d, then dS = P (dP - delta) with
     // P = exp(scale s - lse), so that dP lives for one group only
-    f32x4 sc[NH][4];
+    f32x4 sc[NH][T / 16];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < T / 16; ++j) {
       f32x4 dp[NH];
 #pragma unroll
       for (int a = 0; a < NH; ++a) {
@@ -473,12 +475,12 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
     }
     // steps that cross the diagonal, or hold rows past the view: zero what
     // the row cannot see
-    if (k0 + AT_T > hh + wq0 + 1 || R::WR * (w + 1) > nq) {
+    if (k0 + T > hh + wq0 + 1 || R::WR * (w + 1) > nq) {
 #pragma unroll
       for (int a = 0; a < NH; ++a) {
-        const int lim = R::WR * w + 16 * a + i < nq ? hh + wq0 + 16 * a + i - k0 - 4 * g : -AT_T;
+        const int lim = R::WR * w + 16 * a + i < nq ? hh + wq0 + 16 * a + i - k0 - 4 * g : -T;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < T / 16; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             if (16 * j + r > lim) sc[a][j][r] = 0.f;
@@ -486,7 +488,7 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
     }
     // dQ^T += K^T dS^T: lane (g, i) of half a gets dQ[q = wq0 + 16 a + i][d = 16 jn + 4 g + r]
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
+    for (int s2 = 0; s2 < T / 32; ++s2) {
       bf16x8 sf[NH];
 #pragma unroll
       for (int a = 0; a < NH; ++a) sf[a] = RegB<bf16>::pack(sc[a] + 2 * s2);
@@ -520,9 +522,10 @@ __global__ __launch_bounds__(AT_THR, 2) void k_attn_dq(
 // TFLOP/s).  What bounds it now: two waves a SIMD, each with a chain of LDS
 // reads, products, exponentials and products a step (MFMA busy 40%, LDS 26%).
 // Three waves of one half each: 7,176 us.  Raised priority around the products
-// 6,500 -> 6,340 us; with one half a wave it cost 10%.
+// 6,500 -> 6,340 us; with one half a wave it cost 10%.  At d = 64 the two
+// halves fit three waves a SIMD (30,000 rows, 16 heads: 1,545 -> 1,355 us).
 template <int D, int NH>
-__global__ __launch_bounds__(AT_THR, 2) void k_attn_dkdv(
+__global__ __launch_bounds__(AT_THR, D == 64 ? 3 : 2) void k_attn_dkdv(
     const int32_t* __restrict__ views, const int32_t* __restrict__ kvtiles, int H, float scale,
     const bf16* __restrict__ q, const bf16* __restrict__ kv_k, const bf16* __restrict__ kv_v,
     const bf16* __restrict__ dO, const float* __restrict__ lse, const float* __restrict__ delta,
