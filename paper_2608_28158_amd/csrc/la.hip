@@ -431,7 +431,7 @@ __device__ __forceinline__ void score_block(T* P, const T* Lt, const T* Rt, cons
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) c[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
+#pragma unroll LA_UNROLL<D>
   for (int k = 0; k < D; k += F::KSTEP) {
     const typename F::V a0 = F::template kc<LL>(Lt, rb, k, lane);
     const typename F::V a1 = F::template kc<LL>(Lt, rb + 16, k, lane);
@@ -854,7 +854,7 @@ __global__ __launch_bounds__((Cfg<T, D>::NTHR), (Cfg<T, D>::WPE)) void k_fwd_blo
     // col0 + 16 j + 4g .. + 3
     PackedState<T, C::NT, C::CPW> ps;
     ps.pack(S);
-#pragma unroll 1
+#pragma unroll LA_UNROLL<D>
     for (int it = 0; it < CB / 16; ++it) {
       if (it == 1 && more) fetch<T, D>(pv, v, cs, H, h, t, ROW_REPLAY);
       f32x4 acc[C::CPW];
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__((2 * Cfg<T, D>::NTHR), (Cfg<T, D>::WPE)) void k_bwd
       // 16 it + i, columns col0 + 16 j + 4g .. + 3
       const ChunkRows cur = chunk_rows(sq, c);
       const int g4 = 4 * (ln >> 4);
-#pragma unroll 1
+#pragma unroll LA_UNROLL<D>
       for (int it = 0; it < NIT; ++it) {
         f32x4 acc[C::CPW];
 #pragma unroll
@@ -1268,7 +1268,7 @@ __device__ __forceinline__ void bwd_revorder_rows(
   float xr[CB / 16];
 #pragma unroll
   for (int jt = 0; jt < CB / 16; ++jt) xr[jt] = mt.x[jt * 16 + (lane & 15)];
-#pragma unroll 1
+#pragma unroll LA_UNROLL<D>
   for (int jt = 0; jt < CB / 16; ++jt) {
     const int m = jt * 16 + (lane & 15);
     // side 1: the K values of the lane's row and columns, requested first

@@ -155,6 +155,18 @@ struct Cfg {
   static_assert(CPW >= 1 && NT == NW * CPW, "state split into column strips");
 };
 
+// Unrolling of the row-block and k-step loops of the chunk kernels.  A wave's
+// products of one chunk are a chain of LDS reads, MFMA and stores; at d = 64
+// its state takes a quarter of the registers that it takes at d = 128, and with
+// every step unrolled the reads of one overlap the products of another (18,001
+// rows, 20 heads of 64, bf16, a launch: forward 28.7 -> 25.7 us, forward-order
+// 37.5 -> 34.8, reverse-order 36.6 -> 33.9; 481 rows, 4 heads of 64, float32:
+// 12.8 -> 11.3, 13.1 -> 12.4, 20.8 -> 18.9).  At d = 128 the loops stay rolled:
+// unrolled twice the forward kernels measure the same (they move 4 TB/s) and the
+// reverse-order kernel spills (131k rows, 32 heads: 1,010 -> 1,276 us).
+template <int D>
+constexpr int LA_UNROLL = D == 64 ? 4 : 1;
+
 // 16x16 MFMA tile products.  C[m][n] += sum_k A[m][k] B[k][n] with each
 // operand either k-contiguous ("kc": A stored as rows m, B stored as rows n)
 // or k-major ("km": A stored as rows k with m along the row, B as rows k with
@@ -246,7 +258,7 @@ template <typename T, typename LA, bool A_KM, typename LB, int NJ, bool SWAP = f
 __device__ inline void tile_cols(f32x4* c, const T* A, int am, const T* B, int bn, int k0, int K,
                                  int lane) {
   using F = Frag<T>;
-#pragma unroll 1
+#pragma unroll LA_UNROLL<64 * NJ>
   for (int k = k0; k < K; k += F::KSTEP) {
     const typename F::V a = A_KM ? F::template km<LA>(A, k, am, lane) : F::template kc<LA>(A, am, k, lane);
     if constexpr (EAGER) {
@@ -276,7 +288,7 @@ __device__ inline void tile_cols(f32x4* c, const T* A, int am, const T* B, int b
 template <typename T, typename LA, typename LB, int NT, int CPW, bool EAGER = false>
 __device__ inline void state_update(f32x4* S, const T* A, const T* B, int bn, const float* s, int lane) {
   using F = Frag<T>;
-#pragma unroll 1
+#pragma unroll LA_UNROLL<16 * NT>
   for (int k = 0; k < CB; k += F::KSTEP) {
     typename F::V b[CPW];
     if constexpr (EAGER) {
