@@ -46,6 +46,7 @@ class HartsPlan:
         _lib.check(L.harts_plan_blob(h, self.blob_host.ctypes.data,
                                      self.blob_host.nbytes), "harts_plan_blob")
         self._blob_dev = {}
+        self._la_sizes = {}
 
     def _export(self):
         sizes = dict(self.info)
@@ -69,6 +70,26 @@ class HartsPlan:
         if key in self.arrays:
             return self.arrays[key]
         return self.info[key]
+
+    def la_sizes(self, code, H, d):
+        """Bytes per round of ``harts_la_fwd`` / ``harts_la_bwd`` for H heads of
+        d: (saved, forward workspace keeping the states, without, backward
+        workspace with kept states, without).  They follow from the plan alone
+        and are asked of the library once per (type, heads, head size): five
+        calls a round took 10 us of a small layer call."""
+        key = (code, H, d)
+        if key not in self._la_sizes:
+            L, sz, n = self._L, C.c_size_t(), self.info["n_rounds"]
+
+            def ask(fn, what, *args):
+                _lib.check(fn(self._h, *args, C.byref(sz)), what)
+                return sz.value
+
+            saved = tuple(ask(L.harts_la_saved_size, "harts_la_saved_size", r, code, H, d, d) for r in range(n))
+            ws = (tuple(ask(L.harts_la_workspace_size, "harts_la_workspace_size", r, bwd, code, H, d, d, keep)
+                        for r in range(n)) for bwd, keep in ((0, 1), (0, 0), (1, 1), (1, 0)))
+            self._la_sizes[key] = (saved, *ws)
+        return self._la_sizes[key]
 
     def blob(self, device):
         """Device copy of the descriptor image (uploaded once per device)."""

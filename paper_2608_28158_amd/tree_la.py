@@ -19,8 +19,6 @@ in libharts.
 """
 from __future__ import annotations
 
-import ctypes as C
-
 import torch
 
 from . import _lib
@@ -28,7 +26,7 @@ from .plan import HartsPlan
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _dtype_code(dt):
@@ -58,49 +56,30 @@ class TreeLARunner:
         self.L = _lib.lib()
         self.blob = plan.blob(self.device)
         self.elems = H * d * d
-        sz = C.c_size_t()
-        self.saved_bytes, self.ws_fwd, self.ws_fwd_nosave = [], [], []
-        self.ws_bwd_saved, self.ws_bwd_rec = [], []
-        for r in range(plan.info["n_rounds"]):
-            _lib.check(self.L.harts_la_saved_size(plan.handle, r, self.code, H, d, d,
-                                                  C.byref(sz)), "harts_la_saved_size")
-            self.saved_bytes.append(sz.value)
-            _lib.check(self.L.harts_la_workspace_size(plan.handle, r, 0, self.code, H, d, d, 1,
-                                                      C.byref(sz)), "harts_la_workspace_size")
-            self.ws_fwd.append(sz.value)
-            _lib.check(self.L.harts_la_workspace_size(plan.handle, r, 0, self.code, H, d, d, 0,
-                                                      C.byref(sz)), "harts_la_workspace_size")
-            self.ws_fwd_nosave.append(sz.value)
-            _lib.check(self.L.harts_la_workspace_size(plan.handle, r, 1, self.code, H, d, d, 1,
-                                                      C.byref(sz)), "harts_la_workspace_size")
-            self.ws_bwd_saved.append(sz.value)
-            _lib.check(self.L.harts_la_workspace_size(plan.handle, r, 1, self.code, H, d, d, 0,
-                                                      C.byref(sz)), "harts_la_workspace_size")
-            self.ws_bwd_rec.append(sz.value)
+        (self.saved_bytes, self.ws_fwd, self.ws_fwd_nosave, self.ws_bwd_saved,
+         self.ws_bwd_rec) = plan.la_sizes(self.code, H, d)
 
     # -- helpers -------------------------------------------------------------
     def _stream(self):
-        return C.c_void_p(torch.cuda.current_stream(self.device).cuda_stream)
+        return torch.cuda.current_stream(self.device).cuda_stream
 
     def _bytes(self, n):
         return torch.empty(max(int(n), 16), dtype=torch.uint8, device=self.device)
 
-    def _init_idx(self, r):
-        off = self.plan.rounds[r]["init_idx_off"]
-        return C.c_void_p(self.blob.data_ptr() + off)
+    def _state_gather(self, src, r, dst, add, stream):
+        """dst = src[init_idx] (add 0) or dst[init_idx] += src (add 1), on addresses."""
+        R = self.plan.rounds[r]
+        _lib.check(self.L.harts_state_gather(src, self.blob.data_ptr() + R["init_idx_off"], R["n_seq"],
+                                             self.elems, dst, add, stream), "harts_state_gather")
 
     def gather(self, bank, r):
         n = self.plan.rounds[r]["n_seq"]
         S0 = torch.empty((n, self.H, self.d, self.d), dtype=torch.float32, device=self.device)
-        _lib.check(self.L.harts_state_gather(_ptr(bank), self._init_idx(r), n, self.elems,
-                                             _ptr(S0), 0, self._stream()), "harts_state_gather")
+        self._state_gather(_ptr(bank), r, _ptr(S0), 0, self._stream())
         return S0
 
     def scatter_add(self, dS0, dbank, r):
-        n = self.plan.rounds[r]["n_seq"]
-        _lib.check(self.L.harts_state_gather(_ptr(dS0), self._init_idx(r), n, self.elems,
-                                             _ptr(dbank), 1, self._stream()),
-                   "harts_state_gather")
+        self._state_gather(_ptr(dS0), r, _ptr(dbank), 1, self._stream())
 
     def _check_inputs(self, q, k, v, g):
         Cn = self.plan.info["C"]
@@ -134,14 +113,18 @@ class TreeLARunner:
         S_final = torch.empty((P.info["n_leaves"], H, d, d), dtype=torch.float32,
                               device=self.device) if final_states else None
         saved = []
+        # the rounds run one after another on one stream: one workspace serves all
+        sizes = self.ws_fwd if keep_states else self.ws_fwd_nosave
+        ws = self._bytes(max(sizes, default=0))
+        ws_p, ws_n, stream = _ptr(ws), ws.numel(), self._stream()
+        blob_p, bank_p, S_final_p = _ptr(self.blob), _ptr(bank), _ptr(S_final)
+        q_p, k_p, v_p, g_p, o_p = _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(o)
         for r in range(P.info["n_rounds"]):
             S0 = self.gather(bank, r) if self.gather_init else None
             sv = self._bytes(self.saved_bytes[r]) if keep_states else None
-            ws = self._bytes(self.ws_fwd[r] if keep_states else self.ws_fwd_nosave[r])
             _lib.check(self.L.harts_la_fwd(
-                P.handle, r, _ptr(self.blob), self.code, H, d, d, self.scale,
-                _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(S0), _ptr(o), _ptr(S_final),
-                _ptr(bank), _ptr(sv), _ptr(ws), ws.numel(), self._stream()), "harts_la_fwd")
+                P.handle, r, blob_p, self.code, H, d, d, self.scale, q_p, k_p, v_p, g_p, _ptr(S0), o_p,
+                S_final_p, bank_p, _ptr(sv), ws_p, ws_n, stream), "harts_la_fwd")
             saved.append(sv)
         return dict(o=o, S_final=S_final, bank=bank, saved=saved)
 
@@ -171,23 +154,26 @@ class TreeLARunner:
         rep = torch.empty((max(R, 1), H, 2 * d + 1), dtype=torch.float32, device=self.device)
         # dS0 of every sequence, in sequence (round) order; each round writes its slice
         dS0_seq = torch.empty((P.info["n_seq"], H, d, d), dtype=torch.float32, device=self.device)
-        for r in reversed(range(P.info["n_rounds"])):
-            n = P.rounds[r]["n_seq"]
-            s0 = P.rounds[r]["seq_begin"]
-            dS0 = dS0_seq[s0:s0 + n]
+        n_rounds = P.info["n_rounds"]
+        saved = [None] * n_rounds if recompute else fwd["saved"]
+        # one workspace for all rounds, as in the forward
+        ws = self._bytes(max((w if sv is not None else rec for w, rec, sv in
+                              zip(self.ws_bwd_saved, self.ws_bwd_rec, saved)), default=0))
+        ws_p, ws_n, stream = _ptr(ws), ws.numel(), self._stream()
+        blob_p, bank_p, dSf_p, dbank_p = _ptr(self.blob), _ptr(fwd["bank"]), _ptr(dS_final), _ptr(dbank)
+        q_p, k_p, v_p, g_p, dO_p = _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(dO)
+        dq_p, dk_p, dv_p, dg_p, rep_p = _ptr(dq), _ptr(dk), _ptr(dv), _ptr(dg), _ptr(rep)
+        dS0_base, seq_bytes = _ptr(dS0_seq), 4 * self.elems
+        for r in reversed(range(n_rounds)):
+            dS0_p = dS0_base + P.rounds[r]["seq_begin"] * seq_bytes
             S0 = self.gather(fwd["bank"], r) if self.gather_init else None
-            sv = None if recompute else fwd["saved"][r]
-            ws = self._bytes(self.ws_bwd_rec[r] if sv is None else self.ws_bwd_saved[r])
             _lib.check(self.L.harts_la_bwd(
-                P.handle, r, _ptr(self.blob), self.code, H, d, d, self.scale,
-                _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(S0), _ptr(fwd["bank"]), _ptr(dO),
-                _ptr(dS_final),
-                _ptr(dbank), _ptr(sv), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(dg),
-                _ptr(rep), _ptr(dS0), _ptr(ws), ws.numel(), self._stream()), "harts_la_bwd")
-            self.scatter_add(dS0, dbank, r)
+                P.handle, r, blob_p, self.code, H, d, d, self.scale, q_p, k_p, v_p, g_p, _ptr(S0), bank_p,
+                dO_p, dSf_p, dbank_p, _ptr(saved[r]), dq_p, dk_p, dv_p, dg_p, rep_p, dS0_p, ws_p, ws_n,
+                stream), "harts_la_bwd")
+            self._state_gather(dS0_p, r, dbank_p, 1, stream)
         _lib.check(self.L.harts_replay_reduce(
-            P.handle, _ptr(self.blob), self.code, H, d, d, _ptr(rep), _ptr(dk), _ptr(dv),
-            _ptr(dg), self._stream()), "harts_replay_reduce")
+            P.handle, blob_p, self.code, H, d, d, rep_p, dk_p, dv_p, dg_p, stream), "harts_replay_reduce")
         return dict(dq=dq, dk=dk, dv=dv, dg=dg, dS0_tree=dbank[: P.info["n_trees"]],
                     dS0_seq=dS0_seq, dbank=dbank)
 

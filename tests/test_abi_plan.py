@@ -258,3 +258,25 @@ def test_small_rounds_take_short_blocks(L):
             p.close()
             wide.close()
     assert want[5, 1][0] == 1 and want[1, 4] == [8] and want[1, 1] == [2]
+
+
+@pytest.mark.parametrize("code,H,d", [(0, 4, 64), (1, 4, 64), (1, 3, 128)])
+def test_la_sizes_are_the_librarys(L, code, H, d):
+    """HartsPlan.la_sizes: per round what the library answers, for each type,
+    head count and head size on its own, also when asked again; a size that
+    the library refuses stays refused."""
+    from paper_2608_28158_amd import _lib
+    from paper_2608_28158_amd.plan import HartsPlan
+    p = HartsPlan([-1, 0, 0, 1, 1], [1500, 700, 90, 640, 333], 64, heads=H)
+    p.la_sizes(code, H + 1, d)
+    for _ in range(2):
+        got, sz = p.la_sizes(code, H, d), C.c_size_t()
+        for r in range(p.info["n_rounds"]):
+            assert L.harts_la_saved_size(p.handle, r, code, H, d, d, C.byref(sz)) == 0
+            assert got[0][r] == sz.value
+            for i, (bwd, keep) in enumerate([(0, 1), (0, 0), (1, 1), (1, 0)]):
+                assert L.harts_la_workspace_size(p.handle, r, bwd, code, H, d, d, keep, C.byref(sz)) == 0
+                assert got[1 + i][r] == sz.value
+        with pytest.raises(_lib.HartsError):
+            p.la_sizes(code, H, 80)
+    p.close()
