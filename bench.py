@@ -58,7 +58,7 @@ def la_source_sha(kernel=None):
     elif kernel and kernel.startswith("k_conv"):
         names = ("conv.hip",)
     elif kernel and kernel.startswith("k_attn"):
-        names = ("attn.hip", "la_common.hpp")
+        names = ("attn.hip", "la_common.hpp", "lds_load.hpp")
     else:
         names = ("la.hip", "la_common.hpp")
     h = hashlib.sha256()
