@@ -18,12 +18,12 @@
 // log2(e)-scaled logits.  No atomics, every sum in a fixed order.
 //
 // Both row kernels are bound by the bytes of the logits: the forward reads
-// them at 6.5 TB/s, the backward reads and writes at 5.2 (17,640 rows of
-// 157,184 bf16: 856 and 1,809 us; a large copy moves 5.0 TB/s).  What is left
+// them at 6.5 TB/s, the backward reads and writes at 5.4 (17,640 rows of
+// 157,184 bf16: 858 and 2,040 us; a large copy moves 5.0 TB/s).  What is left
 // to save is launches (the row sums and the target columns were kernels of
-// their own: a pass over 481 rows of 32,008 float32 went from 53 to 38 us)
-// and reads that cannot matter: a row whose positions are all masked has
-// G = 0 (30% of the rows above: 2,177 -> 1,963 us).
+// their own: a pass over 481 rows of 32,008 float32 went from 53 to 40 us).
+// A row without a gradient (G = 0) is read all the same: lse passes over
+// vectors of NaN and -inf, so only the logits tell where 0 times p is NaN.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -39,9 +39,9 @@ typedef __bf16 bf16;
 constexpr int LP_THR = 256;   // threads per row workgroup (and per workgroup of positions)
 // A row of at least LP_WIDE vectors takes 1,024 threads instead of 256: fewer
 // rows are open at a time for the same loads in flight.  Backward of 17,640
-// rows of 157,184 bf16 1,963 -> 1,875 us, forward 944 -> 929; forward of 481
-// rows of 32,008 float32 14.6 -> 13.4 us.  A shorter row would leave most of
-// the 1,024 threads without a vector.
+// rows of 157,184 bf16 2,200 -> 2,040 us (its forward the same within the
+// runs, 790 at best); forward of 481 rows of 32,008 float32 14.7 -> 13.6 us.
+// A shorter row would leave most of the 1,024 threads without a vector.
 constexpr int64_t LP_WIDE = 2048;
 constexpr int LP_THR_W = 1024;
 constexpr int LP_UNROLL = 4;  // 16-byte loads in flight per thread
@@ -50,9 +50,9 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 // Logits of more than LP_STREAM bytes are not in the 256 MB last-level cache
 // when the next kernel comes: the forward then reads and the backward writes
-// them non-temporally.  5.5 GB of bf16 logits: forward 946 -> 856 us, backward
-// 1,869 -> 1,809 us (non-temporal reads made that one 1,926 us); on 62 MB,
-// which the backward finds in the cache, neither is faster.
+// them non-temporally.  5.5 GB of bf16 logits: forward 941 -> 858 us, backward
+// 2,101 -> 2,040 us (2,006 with non-temporal reads as well); on 62 MB, which
+// the backward finds in the cache, neither is faster.
 constexpr int64_t LP_STREAM = int64_t{256} << 20;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(THR) void k_logp_lse(const T* __restrict__ z, int64
         x[u][e] *= kLog2e;
         vm = fmaxf(vm, x[u][e]);
       }
-      if (vm == -INFINITY) continue;  // a vector past the row's end
+      if (vm == -INFINITY) continue;  // past the row's end, or nothing but -inf and NaN
       const float n = fmaxf(m, vm);
       float acc = m == -INFINITY ? 0.f : s * ex2(m - n);
 #pragma unroll
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(THR) void k_logp_grad(const T* __restrict__ z, int6
   const int64_t nvec = V / L::N;
   const int64_t b = row_off[c] < 0 ? 0 : row_off[c];
   const int64_t e = row_off[c + 1] > n_pos ? n_pos : row_off[c + 1];
-  const float ls = lse[c];
+  const float l2 = lse[c] * kLog2e;
   const auto valid = [n_pos](int32_t s) { return s >= 0 && s < n_pos; };
   // G: the positions' gradients are requested together and added in order by
   // every thread from LDS (an invalid entry adds nothing)
@@ -223,31 +223,21 @@ __global__ __launch_bounds__(THR) void k_logp_grad(const T* __restrict__ z, int6
     for (int k = 0; k < n; ++k) Gc += sg[k];
   }
   if (t == 0) G[c] = Gc;
-  const float l2 = ls * kLog2e;
   const float ng = -Gc;
-  if (Gc == 0.f && fabsf(ls) < INFINITY) {
-    // -0 p is -0 (or 0) for every finite probability, and a finite log-sum-exp
-    // has no other: the row is written without reading its logits
-    float x[L::N];
+  for (int64_t i0 = t; i0 < nvec; i0 += static_cast<int64_t>(THR) * LP_UNROLL) {
+    float x[LP_UNROLL][L::N];
 #pragma unroll
-    for (int k = 0; k < L::N; ++k) x[k] = ng;
-    for (int64_t i = t; i < nvec; i += THR) L::template store<NT>(out + i * L::N, x);
-  } else {
-    for (int64_t i0 = t; i0 < nvec; i0 += static_cast<int64_t>(THR) * LP_UNROLL) {
-      float x[LP_UNROLL][L::N];
+    for (int u = 0; u < LP_UNROLL; ++u) {
+      const int64_t i = i0 + static_cast<int64_t>(u) * THR;
+      if (i < nvec) L::template load<false>(row + i * L::N, x[u]);
+    }
 #pragma unroll
-      for (int u = 0; u < LP_UNROLL; ++u) {
-        const int64_t i = i0 + static_cast<int64_t>(u) * THR;
-        if (i < nvec) L::template load<false>(row + i * L::N, x[u]);
-      }
+    for (int u = 0; u < LP_UNROLL; ++u) {
+      const int64_t i = i0 + static_cast<int64_t>(u) * THR;
+      if (i < nvec) {
 #pragma unroll
-      for (int u = 0; u < LP_UNROLL; ++u) {
-        const int64_t i = i0 + static_cast<int64_t>(u) * THR;
-        if (i < nvec) {
-#pragma unroll
-          for (int k = 0; k < L::N; ++k) x[u][k] = ng * ex2(x[u][k] * kLog2e - l2);
-          L::template store<NT>(out + i * L::N, x[u]);
-        }
+        for (int k = 0; k < L::N; ++k) x[u][k] = ng * ex2(x[u][k] * kLog2e - l2);
+        L::template store<NT>(out + i * L::N, x[u]);
       }
     }
   }

@@ -232,3 +232,29 @@ def test_logp_launch_edges(L, Cn, V, dtype):
     assert np.abs(logp - (zd[md, yd] - lse[md]).cpu().numpy())[fine].max() < 1e-5
     assert not dz[0].any() and not dz[1].any()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [808, 17000])
+def test_logp_nan_logits_of_rows_without_gradient(L, V, dtype):
+    """A row's log-sum-exp passes over 16-byte vectors of nothing but NaN and
+    -inf, so it can be finite beside NaN logits: their gradient is NaN (0 times
+    NaN) also in rows whose positions are masked or that have none; the rest
+    of such a row is zero."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    z = (torch.randn((6, V), device="cuda", generator=gen) * 2).to(tdt)
+    bad = torch.zeros((6, V), dtype=torch.bool, device="cuda")
+    z[1, 16:24] = float("nan")          # masked positions
+    z[2, 16:24] = float("-inf")         # no position
+    z[2, 18] = float("nan")
+    z[4, V - 8:] = float("nan")         # gradients that cancel
+    bad[1, 16:24] = bad[2, 18] = bad[4, V - 8:] = True
+    m, y = np.array([0, 1, 1, 3, 4, 4, 5], np.int32), np.array([3, 4, 5, 6, 7, 9, 8], np.int32)
+    g = np.array([1, 0, 0, 0, 0.5, -0.5, 1], np.float32)
+    off = np.concatenate([[0], np.cumsum(np.bincount(m, minlength=6))]).astype(np.int64)
+    _, dz, row_g = run_logp(L, z, m, y, off, np.arange(len(m), dtype=np.int32), g)
+    assert torch.equal(torch.isnan(dz), bad)
+    rest = dz[1:5].masked_fill(bad[1:5], 0)
+    rest[3, 7] = rest[3, 9] = 0         # the targets whose gradients cancel over the row
+    assert not rest.any() and not row_g[1:5].any()
