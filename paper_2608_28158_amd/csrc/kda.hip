@@ -564,7 +564,10 @@ __global__ __launch_bounds__(NT) void k_kda_prep(const int32_t* __restrict__ chu
     const int i = p / KB, j = p % KB;
     const f32x4 x = ld4(sL + i * LT + j);
     *reinterpret_cast<f32x4*>(w + Y::LINV + p) = x;
-    *reinterpret_cast<f32x4*>(sA + i * LT + j) = x * ld4(sb + j);
+    const f32x4 y = x * ld4(sb + j);
+    // (the zeros above the diagonal stay zeros where beta is not finite)
+    *reinterpret_cast<f32x4*>(sA + i * LT + j) =
+        f32x4{j <= i ? y[0] : 0.f, j + 1 <= i ? y[1] : 0.f, j + 2 <= i ? y[2] : 0.f, j + 3 <= i ? y[3] : 0.f};
   }
   pk.template store<LW>(sK, t);
   pv.template store<LW>(sQ, t);

@@ -272,3 +272,33 @@ def test_kda_backward_unaligned_rows(dtype):
         assert torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), n
     # rows replayed elsewhere go to the slots, all others to dv
     assert int(torch.isnan(outs[0][5]).any(-1).any(-1).sum()) == sz.n_multi
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 128)])
+def test_kda_non_finite_beta_leaves_earlier_queries(dtype, d, bad):
+    """A query's gradient depends on no later row: with a beta that is not
+    finite in a chunk's first 16 rows, the rows before it keep their dq (0
+    times that beta must not reach them); so do a fork's other branch and the
+    other head.  (In later 16-row blocks the products of whole blocks with
+    L^-1 spread it over the block.)"""
+    from paper_2608_28158_amd.kda import KdaRunner
+    from paper_2608_28158_amd.plan import HartsPlan
+    parent, seg_len, H = [-1, 0, 0], [100, 90, 70], 2
+    plan = HartsPlan(parent, seg_len, 64, heads=H)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v, g, beta, dO, S0, dSf = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in draw(
+        260, H, d, 1, 2, 9, dtype == "bf16"))
+    q, k, v, dO = (t.to(tdt) for t in (q, k, v, dO))
+    run, outs = KdaRunner(plan, H, d, tdt), []
+    row = int(plan["seg_row"][1]) + 41          # position 141 of its trajectory: chunk row 13
+    for x in (None, bad):
+        b = beta.clone()
+        if x is not None:
+            b[row, 1] = x
+        run.forward(q, k, v, g, b, S0, d ** -0.5)
+        outs.append(run.backward(dO, dSf)["dq"].clone())
+    keep = torch.ones(260, dtype=torch.bool, device="cuda")
+    keep[row:int(plan["seg_row"][1]) + 90] = False
+    assert torch.equal(outs[0][:, 0], outs[1][:, 0]) and torch.equal(outs[0][keep], outs[1][keep])
+    assert not torch.isfinite(outs[1][row + 1:row + 30, 1]).any()
