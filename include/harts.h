@@ -459,7 +459,8 @@ int harts_conv_bwd(int32_t dtype, int64_t C, int32_t Cch, int32_t w, const void*
  *   the backward), from q [C, H, d] and the key/value views [n_kv, H, d].
  * harts_attn_bwd (device) -- from dO [C, H, d]: dq [C, H, d] bf16 (written),
  *   dk_view, dv_view [n_kv, H, d] float32 (written); delta [C, H] float32 is
- *   scratch (dO . o per row).
+ *   scratch (dO . o per row).  dq may overlap o (one launch more), no other
+ *   input.
  * harts_attn_scatter (device) -- dst [C, H, d] bf16 = sum over each row's
  *   view rows of src [n_kv, H, d] float32, in row_ent order (deterministic).
  * Pointers to row tensors 16-byte aligned.  Errors: HARTS_EINVAL (NULL,

@@ -376,13 +376,15 @@ __device__ inline void at_delta(int64_t e0, int64_t n, const bf16* __restrict__ 
 // and V tiles (each fragment feeding all halves), dS = P (dP - delta),
 // dQ += dS K.  The workgroups past the tiles' write delta of all C rows for
 // the dk/dv kernel: as a kernel of their own (one thread an entry) they took
-// 215 us of an 11.8 ms backward and a launch of every small one.
+// 215 us of an 11.8 ms backward and a launch of every small one.  Where dq is
+// written over o they go first, in a launch of their own, and the tiles read
+// delta and not o (have_delta).
 template <int D, int NH>
 __global__ __launch_bounds__(AT_THR, D == 64 && NH == 2 ? 4 : 2) void k_attn_dq(
     const int32_t* __restrict__ views, const int32_t* __restrict__ qtiles, int H, float scale,
     const bf16* __restrict__ q, const bf16* __restrict__ kv_k, const bf16* __restrict__ kv_v,
     const bf16* __restrict__ o, const bf16* __restrict__ dO, const float* __restrict__ lse, uint32_t n_tile_wg,
-    int64_t n_rows, float* __restrict__ delta, bf16* __restrict__ dq) {
+    int64_t n_rows, int have_delta, float* __restrict__ delta, bf16* __restrict__ dq) {
   using F = Frag<bf16>;
   using L = AtTile<D>;
   using R = AtRows<NH>;
@@ -414,18 +416,22 @@ __global__ __launch_bounds__(AT_THR, D == 64 && NH == 2 ? 4 : 2) void k_attn_dq(
 #pragma unroll
   for (int a = 0; a < NH; ++a) {
     const int r = min(R::WR * w + 16 * a, nq - 1), last = nq - 1 - r;
-    bf16x8 of[NS];
-    at_frags<D>(qf[a], q, qrow0 + t0 + r, last, H, h, lane);
-    at_frags<D>(df[a], dO, qrow0 + t0 + r, last, H, h, lane);
-    at_frags<D>(of, o, qrow0 + t0 + r, last, H, h, lane);
-    float x = 0.f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x = fmaf(static_cast<float>(of[s][e]), static_cast<float>(df[a][s][e]), x);
-    dl[a] = row_sum4(x);
     const bool live = R::WR * w + 16 * a + i < nq;
     const int64_t row = qrow0 + (live ? wq0 + 16 * a + i : t0);
+    at_frags<D>(qf[a], q, qrow0 + t0 + r, last, H, h, lane);
+    at_frags<D>(df[a], dO, qrow0 + t0 + r, last, H, h, lane);
+    if (have_delta) {
+      dl[a] = delta[row * H + h];
+    } else {
+      bf16x8 of[NS];
+      at_frags<D>(of, o, qrow0 + t0 + r, last, H, h, lane);
+      float x = 0.f;
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x = fmaf(static_cast<float>(of[s][e]), static_cast<float>(df[a][s][e]), x);
+      dl[a] = row_sum4(x);
+    }
     l2[a] = live ? lse[row * H + h] * AT_LOG2E : 0.f;
   }
   const bool wave_live = R::WR * w < nq;
@@ -840,10 +846,19 @@ extern "C" int harts_attn_bwd(const int32_t* views, const int32_t* qtiles, int64
   const auto* bd = static_cast<const bf16*>(dO);
   auto* bdq = static_cast<bf16*>(dq);
   const int64_t n = C * H;
+  // dq over o: a workgroup's delta would read what another's dq has written
+  const uintptr_t o0 = reinterpret_cast<uintptr_t>(o), q0 = reinterpret_cast<uintptr_t>(dq);
+  const bool over = (o0 < q0 ? q0 - o0 : o0 - q0) < static_cast<uintptr_t>(n) * d * sizeof(bf16);
   const auto launch_dq = [&](auto kernel, int sub) {
     const uint32_t tiles = static_cast<uint32_t>(n_qtiles * sub * H);
-    hipLaunchKernelGGL(kernel, dim3(tiles + static_cast<uint32_t>((n + AT_THR - 1) / AT_THR)), dim3(AT_THR), 0, s,
-                       views, qtiles, H, scale, bq, bk, bv, bo, bd, lse, tiles, n, delta, bdq);
+    const uint32_t rows = static_cast<uint32_t>((n + AT_THR - 1) / AT_THR);
+    const auto go = [&](uint32_t t, uint32_t r, int have_delta) {
+      if (t + r > 0)
+        hipLaunchKernelGGL(kernel, dim3(t + r), dim3(AT_THR), 0, s, views, qtiles, H, scale, bq, bk, bv, bo, bd, lse,
+                           t, n, have_delta, delta, bdq);
+    };
+    if (over) go(0, rows, 0);
+    go(tiles, over ? 0 : rows, over);
   };
   if (at_fills(n_qtiles, H)) {
     if (d == 128) launch_dq(k_attn_dq<128, 2>, AtRows<2>::SUB);

@@ -261,3 +261,46 @@ def test_attn_bwd_parts_by_themselves(L):
     ref = (full["o"].double() * dO.double()).sum(-1)
     # float32 sum of 64 products of magnitude about 1
     assert float((parts[1][3].double() - ref).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [2, 64], ids=["64-row workgroups", "128-row workgroups"])
+@pytest.mark.parametrize("shift", [0, 1, -40])
+def test_attn_bwd_dq_over_o(L, d, H, shift):
+    """dq written into o's memory, in place or shift rows off: dk, dv and delta
+    are those of separate buffers, dq up to the order of delta's sum."""
+    from paper_2608_28158_amd import _lib
+    from paper_2608_28158_amd.plan import HartsPlan
+    label, parent, seg_len = SMALL[1]
+    plan = HartsPlan(parent, seg_len, 64)
+    Cn, scale = int(np.sum(seg_len)), d ** -0.5
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q, k, v, dO = (torch.randn((Cn, H, d), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(4))
+    full = run_attn(L, plan, q, k, v, dO, H, d, scale)
+    lay, views, kv_rows, qt, kt, _, _ = views_of(L, plan)
+    assert (lay.n_qtiles * H >= 512) == (H == 64)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    vd, kr, qd, kd = (dev(a) for a in (views, kv_rows, qt, kt))
+    kvk, kvv = k[kr.long()].contiguous(), v[kr.long()].contiguous()
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    outs = []
+    for both in (False, True):
+        buf = torch.full((Cn + abs(shift), H, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        o = buf[max(0, -shift):][:Cn]
+        o.copy_(full["o"])
+        dq = buf[max(0, shift):][:Cn] if both else torch.full_like(q, float("nan"))
+        delta = torch.full((Cn, H), float("nan"), device="cuda")
+        dkv, dvv = (torch.full((lay.n_kv, H, d), float("nan"), device="cuda") for _ in range(2))
+        _lib.check(L.harts_attn_bwd(_p(vd), _p(qd), lay.n_qtiles, _p(kd), lay.n_kvtiles, Cn, H, d, C.c_float(scale),
+                                    _p(q), _p(kvk), _p(kvv), _p(o), _p(full["lse"]), _p(dO), _p(delta), _p(dq),
+                                    _p(dkv), _p(dvv), st), "harts_attn_bwd")
+        outs.append((dq.float(), delta, dkv, dvv))
+    assert torch.equal(outs[0][0], full["dq"].float())
+    for a, b in zip(outs[0][1:], outs[1][1:]):
+        assert torch.equal(a, b)
+    # delta's sum in another order turns the rounding to bf16 of an entry of dS
+    # now and then, which moves dq by 2^-8 of that key's term of the sum (a
+    # part of a row's largest values), and then that of dq itself
+    a, b = outs[0][0], outs[1][0]
+    assert float((a - b).abs().max()) <= 2.0 ** -7 * float(a.abs().max())
+    assert float((a - b).norm()) <= 2.0 ** -10 * float(a.norm())
