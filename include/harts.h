@@ -165,7 +165,10 @@ int harts_plan_export(const harts_plan_t* plan, const harts_plan_arrays* dst);
  * does).  min_blocks = 0 chooses ceil(896 / H), i.e. about 896 (block, head)
  * workgroups per round, and a round that 8-chunk blocks leave below that
  * takes the smallest of 4, 2, 1 with at most 256 (block, head) workgroups
- * (8 if none has); a plan fresh from harts_plan is set for H = 16.
+ * (8 if none has); a plan fresh from harts_plan is set for H = 16.  The device
+ * calls take any number of heads: one with more than 256 (block, head)
+ * workgroups of such a round runs it in 8-chunk blocks, from a second set of
+ * tables in the blob (harts_plan_round_info describes the first).
  * Only the device descriptor image and the per-round block facts change:
  * fetch harts_plan_get_info / harts_plan_round_info / harts_plan_blob again
  * afterwards.  Results of the device calls do not depend on the blocking

@@ -1748,7 +1748,7 @@ struct Sizes {
 };
 
 Sizes sizes(const harts_plan_t* p, int32_t round, int32_t H, int32_t D) {
-  const RoundLayout& L = p->rounds[round];
+  const RoundLayout& L = round_layout(*p, round, H);
   Sizes s{};
   const size_t nsw = static_cast<size_t>(D) * D / 4 / SCAN_THR;
   s.blk_state = align256(static_cast<size_t>(L.n_blk) * H * D * D * sizeof(float));
@@ -1771,9 +1771,9 @@ struct Blob {
   const int32_t* init_idx;
 };
 
-Blob blob_ptrs(const harts_plan_t* p, int32_t round, const void* d_blob) {
+Blob blob_ptrs(const harts_plan_t* p, int32_t round, int32_t H, const void* d_blob) {
   const int32_t* b = static_cast<const int32_t*>(d_blob);
-  const RoundLayout& L = p->rounds[round];
+  const RoundLayout& L = round_layout(*p, round, H);
   return Blob{b + L.seq_tab, b + L.blk_tab, b + L.blk_launch, b + p->off_replay_row, b + L.init_idx};
 }
 
@@ -1782,7 +1782,7 @@ Blob blob_ptrs(const harts_plan_t* p, int32_t round, const void* d_blob) {
 template <typename T, int D>
 int launch_blocksum(const harts_plan_t* p, int32_t round, const Blob& B, int H, const void* k,
                     const void* v, const float* g, float* dSb, float* gam, int skip1, hipStream_t s) {
-  const RoundLayout& L = p->rounds[round];
+  const RoundLayout& L = round_layout(*p, round, H);
   ProfScope ps("k_blocksum", s);
   hipLaunchKernelGGL((k_blocksum<T, D>), dim3(L.n_blk * H), dim3(Cfg<T, D>::NTHR), 0, s, B.seq_tab,
                      B.blk_tab, B.blk_launch, B.replay_row, H, static_cast<const T*>(k),
@@ -1796,7 +1796,7 @@ template <int D>
 int launch_fwd_scan(const harts_plan_t* p, int32_t round, const Blob& B, int H, const InitSrc& is,
                     const float* dSb, const float* gam, float* S_end, float* bank, float* S_final,
                     int skip1, hipStream_t s) {
-  const RoundLayout& L = p->rounds[round];
+  const RoundLayout& L = round_layout(*p, round, H);
   constexpr int NSW = D * D / 4 / SCAN_THR;
   ProfScope ps("k_fwd_blockscan", s);
   hipLaunchKernelGGL((k_fwd_blockscan<D>), dim3(L.n_seq * NSW, H), dim3(SCAN_THR), 0, s,
@@ -1808,9 +1808,9 @@ template <typename T, int D>
 int run_fwd(const harts_plan_t* p, int32_t round, const void* d_blob, int H, float scale,
             const void* q, const void* k, const void* v, const float* g, const float* S0, void* o,
             float* S_final, float* bank, char* saved, char* ws, hipStream_t s) {
-  const RoundLayout& L = p->rounds[round];
+  const RoundLayout& L = round_layout(*p, round, H);
   const Sizes z = sizes(p, round, H, D);
-  const Blob B = blob_ptrs(p, round, d_blob);
+  const Blob B = blob_ptrs(p, round, H, d_blob);
   float* dSb = reinterpret_cast<float*>(ws);
   float* S_end = reinterpret_cast<float*>(saved);
   float* gam = reinterpret_cast<float*>(saved + z.blk_state);
@@ -1840,9 +1840,9 @@ int run_bwd(const harts_plan_t* p, int32_t round, const void* d_blob, int H, flo
             const float* bank, const void* dO, const float* dS_final, const float* dbank, const char* saved,
             char* ws, void* dq, void* dk, void* dv, float* dg, float* rep_grad, float* dS0,
             hipStream_t s) {
-  const RoundLayout& L = p->rounds[round];
+  const RoundLayout& L = round_layout(*p, round, H);
   const Sizes z = sizes(p, round, H, D);
-  const Blob B = blob_ptrs(p, round, d_blob);
+  const Blob B = blob_ptrs(p, round, H, d_blob);
   const InitSrc is{S0, bank, B.init_idx};
   char* w = ws;
   float* U = reinterpret_cast<float*>(w);

@@ -45,17 +45,6 @@ int32_t default_min_blocks(int32_t H) {
 
 namespace {
 
-// A round that cannot reach the target even with 8-chunk blocks takes 4, 2 or
-// 1 chunks per block, as few as keep its (block, head) workgroups within one
-// for each of the 256 CUs: its time is the chain of chunks of a block.  With
-// 8, 4, 2 and 1 chunks per block, forward + recompute + backward: 6,463 rows,
-// 4 heads of 128 (60 workgroups with 8): 320, 230, 200, 245 us; 3,476 rows, 4
-// heads of 64 (44): 213, 154, 132, 134 us; 26,519 rows, 3 heads of 64 (93):
-// 237, 187, 207, 280 us; but 12,140 rows, 16 heads of 64 (240): 250, 263, 300,
-// 410 us.  Within this bound the scratch of a round also stays below 32 MiB,
-// half of what harts_la_fwd_noalloc holds.
-constexpr int64_t kShortUnits = 256;
-
 struct Builder {
   int32_t n;
   int64_t B;
@@ -396,6 +385,90 @@ struct Builder {
     return static_cast<int32_t>(total);
   }
 
+  // the sequence, block and launch tables of one round, in the layout's blocks
+  void fill_round(RoundLayout& L) {
+    harts_plan_s& p = *P;
+    int32_t* b = p.blob.data();
+    int64_t chunk_off = 0;
+    int64_t blk_next = 0;
+    int32_t max_seq_blocks = 0;
+    for (int32_t li = 0; li < L.n_seq; ++li) {
+      const int32_t i = L.seq_begin + li;
+      const int64_t tok = p.seq_n_replay[i] + p.seq_n_own[i];
+      const int64_t nc = (tok + B - 1) / B;
+      int32_t* e = b + L.seq_tab + int64_t(li) * SEQ_WORDS;
+      e[SEQ_CHUNK_OFF] = static_cast<int32_t>(chunk_off);
+      e[SEQ_N_TOK] = static_cast<int32_t>(tok);
+      e[SEQ_N_REPLAY] = static_cast<int32_t>(p.seq_n_replay[i]);
+      e[SEQ_REPLAY_OFF] = static_cast<int32_t>(p.seq_replay_off[i]);
+      e[SEQ_OWN_ROW] = static_cast<int32_t>(p.seq_row[i]);
+      e[SEQ_INIT_BANK] = p.seq_init_bank[i];
+      e[SEQ_FINAL_LEAF] = p.seq_final_leaf[i];
+      e[SEQ_REQ_OFF] = p.seq_req_off[i];
+      e[SEQ_N_REQ] = p.seq_req_off[i + 1] - p.seq_req_off[i];
+      e[SEQ_N_CHUNKS] = static_cast<int32_t>(nc);
+      b[L.init_idx + li] = p.seq_init_bank[i];
+      // blocks of this sequence
+      e[SEQ_BLK_OFF] = static_cast<int32_t>(blk_next);
+      int32_t nb = 0;
+      int32_t c0 = 0;
+      int32_t rq = p.seq_req_off[i];
+      const int32_t rq_end = p.seq_req_off[i + 1];
+      while (c0 < nc) {
+        int32_t c1 = std::min<int32_t>(static_cast<int32_t>(nc), c0 + L.block_chunks);
+        while (rq < rq_end && p.req_chunk[rq] <= c0) ++rq;
+        int32_t end_bank = -1;
+        if (rq < rq_end && p.req_chunk[rq] <= c1) {
+          c1 = p.req_chunk[rq];
+          end_bank = p.req_bank[rq];
+        }
+        int32_t* bk = b + L.blk_tab + blk_next * BLK_WORDS;
+        bk[BLK_SEQ] = li;
+        bk[BLK_C0] = c0;
+        bk[BLK_NC] = c1 - c0;
+        bk[BLK_IDX] = nb;
+        bk[BLK_END_BANK] = end_bank;
+        ++blk_next;
+        ++nb;
+        c0 = c1;
+      }
+      e[SEQ_N_BLK] = nb;
+      max_seq_blocks = std::max(max_seq_blocks, nb);
+      for (int64_t c = 0; c < nc; ++c) {
+        b[L.chunk_tab + 2 * (chunk_off + c)] = li;
+        b[L.chunk_tab + 2 * (chunk_off + c) + 1] = static_cast<int32_t>(c);
+      }
+      chunk_off += nc;
+    }
+    L.max_seq_blocks = max_seq_blocks;
+    // launch order of the block kernels: longest block first (stable), so
+    // that the last workgroups to start are the shortest ones
+    std::vector<int32_t> order(L.n_blk);
+    for (int32_t j = 0; j < L.n_blk; ++j) order[j] = j;
+    const int32_t* bt = b + L.blk_tab;
+    std::stable_sort(order.begin(), order.end(), [bt](int32_t x, int32_t y) {
+      return bt[x * BLK_WORDS + BLK_NC] > bt[y * BLK_WORDS + BLK_NC];
+    });
+    for (int32_t j = 0; j < L.n_blk; ++j) {
+      const int32_t* bk = bt + order[j] * BLK_WORDS;
+      const int32_t* e = b + L.seq_tab + int64_t(bk[BLK_SEQ]) * SEQ_WORDS;
+      int32_t* ln = b + L.blk_launch + int64_t(j) * LCH_WORDS;
+      ln[LCH_BLK] = order[j];
+      ln[LCH_SEQ] = bk[BLK_SEQ];
+      ln[LCH_C0] = bk[BLK_C0];
+      ln[LCH_NC] = bk[BLK_NC];
+      ln[LCH_IDX] = bk[BLK_IDX];
+      ln[LCH_N_BLK] = e[SEQ_N_BLK];
+      ln[LCH_FINAL_LEAF] = e[SEQ_FINAL_LEAF];
+      ln[LCH_INIT_BANK] = e[SEQ_INIT_BANK];
+      ln[LCH_N_TOK] = e[SEQ_N_TOK];
+      ln[LCH_N_REPLAY] = e[SEQ_N_REPLAY];
+      ln[LCH_REPLAY_OFF] = e[SEQ_REPLAY_OFF];
+      ln[LCH_OWN_ROW] = e[SEQ_OWN_ROW];
+      ln[LCH_CHUNK_OFF] = e[SEQ_CHUNK_OFF];
+    }
+  }
+
   void build_blob() {
     harts_plan_s& p = *P;
     p.blob.clear();
@@ -404,6 +477,7 @@ struct Builder {
     const int32_t min_blocks = p.min_blocks;
     int64_t off = 0;
     p.rounds.assign(K, RoundLayout{});
+    p.rounds8.assign(K, RoundLayout{});
     p.n_chunks = 0;
     for (int32_t r = 0; r < K; ++r) {
       RoundLayout& L = p.rounds[r];
@@ -429,7 +503,14 @@ struct Builder {
       for (const int32_t cand : cands) {
         if (count_blocks(L, cand) >= min_blocks) { L.block_chunks = cand; break; }
       }
-      // a round too small for that takes shorter blocks still (kShortUnits)
+      // A round that cannot reach the target even with 8-chunk blocks takes 4,
+      // 2 or 1 chunks per block, as few as keep its (block, head) workgroups
+      // within one for each of the 256 CUs (kShortUnits): its time is the chain
+      // of chunks of a block.  With 8, 4, 2 and 1 chunks per block, forward +
+      // recompute + backward: 6,463 rows, 4 heads of 128 (60 workgroups with
+      // 8): 320, 230, 200, 245 us; 3,476 rows, 4 heads of 64 (44): 213, 154,
+      // 132, 134 us; 26,519 rows, 3 heads of 64 (93): 237, 187, 207, 280 us;
+      // but 12,140 rows, 16 heads of 64 (240): 250, 263, 300, 410 us.
       if (p.short_heads > 0 && count_blocks(L, 8) < min_blocks) {
         for (const int32_t cand : {4, 2, 1}) {
           if (int64_t{count_blocks(L, cand)} * p.short_heads > kShortUnits) break;
@@ -447,6 +528,18 @@ struct Builder {
       off = align_up(off + int64_t(L.n_blk) * BLK_WORDS);
       L.blk_launch = off;
       off = align_up(off + int64_t(L.n_blk) * LCH_WORDS);
+      RoundLayout& L8 = p.rounds8[r];
+      L8 = L;
+      if (L.block_chunks < 8) {   // the second set of tables (round_layout)
+        L8.block_chunks = 8;
+        L8.n_blk = count_blocks(L8, 8);
+        L8.seq_tab = off;
+        off = align_up(off + int64_t(L.n_seq) * SEQ_WORDS);
+        L8.blk_tab = off;
+        off = align_up(off + int64_t(L8.n_blk) * BLK_WORDS);
+        L8.blk_launch = off;
+        off = align_up(off + int64_t(L8.n_blk) * LCH_WORDS);
+      }
     }
     p.off_replay_row = off;
     off = align_up(off + p.R);
@@ -476,85 +569,8 @@ struct Builder {
     p.blob.assign(std::max<int64_t>(off, kAlignWords), 0);
     int32_t* b = p.blob.data();
     for (int32_t r = 0; r < K; ++r) {
-      RoundLayout& L = p.rounds[r];
-      int64_t chunk_off = 0;
-      int64_t blk_next = 0;
-      int32_t max_seq_blocks = 0;
-      for (int32_t li = 0; li < L.n_seq; ++li) {
-        const int32_t i = L.seq_begin + li;
-        const int64_t tok = p.seq_n_replay[i] + p.seq_n_own[i];
-        const int64_t nc = (tok + B - 1) / B;
-        int32_t* e = b + L.seq_tab + int64_t(li) * SEQ_WORDS;
-        e[SEQ_CHUNK_OFF] = static_cast<int32_t>(chunk_off);
-        e[SEQ_N_TOK] = static_cast<int32_t>(tok);
-        e[SEQ_N_REPLAY] = static_cast<int32_t>(p.seq_n_replay[i]);
-        e[SEQ_REPLAY_OFF] = static_cast<int32_t>(p.seq_replay_off[i]);
-        e[SEQ_OWN_ROW] = static_cast<int32_t>(p.seq_row[i]);
-        e[SEQ_INIT_BANK] = p.seq_init_bank[i];
-        e[SEQ_FINAL_LEAF] = p.seq_final_leaf[i];
-        e[SEQ_REQ_OFF] = p.seq_req_off[i];
-        e[SEQ_N_REQ] = p.seq_req_off[i + 1] - p.seq_req_off[i];
-        e[SEQ_N_CHUNKS] = static_cast<int32_t>(nc);
-        b[L.init_idx + li] = p.seq_init_bank[i];
-        // blocks of this sequence
-        e[SEQ_BLK_OFF] = static_cast<int32_t>(blk_next);
-        int32_t nb = 0;
-        int32_t c0 = 0;
-        int32_t rq = p.seq_req_off[i];
-        const int32_t rq_end = p.seq_req_off[i + 1];
-        while (c0 < nc) {
-          int32_t c1 = std::min<int32_t>(static_cast<int32_t>(nc), c0 + L.block_chunks);
-          while (rq < rq_end && p.req_chunk[rq] <= c0) ++rq;
-          int32_t end_bank = -1;
-          if (rq < rq_end && p.req_chunk[rq] <= c1) {
-            c1 = p.req_chunk[rq];
-            end_bank = p.req_bank[rq];
-          }
-          int32_t* bk = b + L.blk_tab + blk_next * BLK_WORDS;
-          bk[BLK_SEQ] = li;
-          bk[BLK_C0] = c0;
-          bk[BLK_NC] = c1 - c0;
-          bk[BLK_IDX] = nb;
-          bk[BLK_END_BANK] = end_bank;
-          ++blk_next;
-          ++nb;
-          c0 = c1;
-        }
-        e[SEQ_N_BLK] = nb;
-        max_seq_blocks = std::max(max_seq_blocks, nb);
-        for (int64_t c = 0; c < nc; ++c) {
-          b[L.chunk_tab + 2 * (chunk_off + c)] = li;
-          b[L.chunk_tab + 2 * (chunk_off + c) + 1] = static_cast<int32_t>(c);
-        }
-        chunk_off += nc;
-      }
-      L.max_seq_blocks = max_seq_blocks;
-      // launch order of the block kernels: longest block first (stable), so
-      // that the last workgroups to start are the shortest ones
-      std::vector<int32_t> order(L.n_blk);
-      for (int32_t j = 0; j < L.n_blk; ++j) order[j] = j;
-      const int32_t* bt = b + L.blk_tab;
-      std::stable_sort(order.begin(), order.end(), [bt](int32_t x, int32_t y) {
-        return bt[x * BLK_WORDS + BLK_NC] > bt[y * BLK_WORDS + BLK_NC];
-      });
-      for (int32_t j = 0; j < L.n_blk; ++j) {
-        const int32_t* bk = bt + order[j] * BLK_WORDS;
-        const int32_t* e = b + L.seq_tab + int64_t(bk[BLK_SEQ]) * SEQ_WORDS;
-        int32_t* ln = b + L.blk_launch + int64_t(j) * LCH_WORDS;
-        ln[LCH_BLK] = order[j];
-        ln[LCH_SEQ] = bk[BLK_SEQ];
-        ln[LCH_C0] = bk[BLK_C0];
-        ln[LCH_NC] = bk[BLK_NC];
-        ln[LCH_IDX] = bk[BLK_IDX];
-        ln[LCH_N_BLK] = e[SEQ_N_BLK];
-        ln[LCH_FINAL_LEAF] = e[SEQ_FINAL_LEAF];
-        ln[LCH_INIT_BANK] = e[SEQ_INIT_BANK];
-        ln[LCH_N_TOK] = e[SEQ_N_TOK];
-        ln[LCH_N_REPLAY] = e[SEQ_N_REPLAY];
-        ln[LCH_REPLAY_OFF] = e[SEQ_REPLAY_OFF];
-        ln[LCH_OWN_ROW] = e[SEQ_OWN_ROW];
-        ln[LCH_CHUNK_OFF] = e[SEQ_CHUNK_OFF];
-      }
+      fill_round(p.rounds[r]);
+      if (p.rounds8[r].seq_tab != p.rounds[r].seq_tab) fill_round(p.rounds8[r]);
     }
     for (int64_t j = 0; j < p.R; ++j) b[p.off_replay_row + j] = static_cast<int32_t>(p.replay_row[j]);
     for (size_t j = 0; j < p.req_chunk.size(); ++j) {
@@ -598,6 +614,7 @@ extern "C" int harts_plan_set_blocks(harts_plan_t* p, int32_t H, int32_t min_blo
     set_error("harts_plan_set_blocks: out of host memory (the plan's device tables are gone)");
     p->blob.clear();
     p->rounds.clear();
+    p->rounds8.clear();
     return HARTS_ENOMEM;
   }
   set_error("");

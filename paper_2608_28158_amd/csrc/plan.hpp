@@ -71,6 +71,11 @@ struct RoundLayout {
   int64_t chunk_tab = 0;  // int32 offset of the [n_chunks][2] chunk table
 };
 
+// A round that is too small to fill the GPU takes blocks shorter than 8 chunks
+// (plan.cpp), as long as they give a call at most this many (block, head)
+// workgroups.
+constexpr int64_t kShortUnits = 256;
+
 }  // namespace harts
 
 struct harts_plan_s {
@@ -94,10 +99,23 @@ struct harts_plan_s {
   // device descriptor image (int32 words) and its layout
   std::vector<int32_t> blob;
   std::vector<harts::RoundLayout> rounds;
+  std::vector<harts::RoundLayout> rounds8;  // the same rounds without blocks shorter than 8 chunks
   int64_t off_replay_row = 0, off_req_chunk = 0, off_req_bank = 0;
   int64_t off_red_rows = 0, off_red_off = 0, off_red_idx = 0, n_red = 0;
 };
 
 namespace harts {
 void set_error(const std::string& msg);
+
+// The tables of a round for a call with H heads.  The plan was cut for one
+// number of heads and a call may have more: where short blocks would give it
+// more than kShortUnits workgroups it runs, and sizes its scratch by, blocks of
+// 8 chunks.  (2,000 rows, 128 heads of 128, cut for 16: 1,060 us in short
+// blocks, 832 in 8-chunk ones.)  Short blocks' scratch is thus at most 2 x 256
+// states of 64 KiB, 32 MiB, and the log-decays: within the 64 MiB that
+// harts_la_fwd_noalloc holds, whatever the call's heads.
+inline const RoundLayout& round_layout(const harts_plan_s& p, int32_t round, int32_t H) {
+  const RoundLayout& L = p.rounds[round];
+  return L.block_chunks >= 8 || L.n_blk * int64_t{H} <= kShortUnits ? L : p.rounds8[round];
+}
 }

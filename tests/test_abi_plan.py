@@ -280,3 +280,77 @@ def test_la_sizes_are_the_librarys(L, code, H, d):
         with pytest.raises(_lib.HartsError):
             p.la_sizes(code, H, 80)
     p.close()
+
+
+def count_blocks(plan, r, chunks):
+    """Blocks of round r cut at requested boundaries and every ``chunks`` chunks."""
+    n, off, req = 0, plan["seq_req_off"], plan["req_chunk"]
+    for i in range(plan.rounds[r]["seq_begin"], plan.rounds[r]["seq_begin"] + plan.rounds[r]["n_seq"]):
+        nc = -(-int(plan["seq_n_replay"][i] + plan["seq_n_own"][i]) // 64)
+        cuts = sorted({0, nc} | {int(c) for c in req[off[i]:off[i + 1]] if c < nc})
+        n += sum(-(-(b - a) // chunks) for a, b in zip(cuts, cuts[1:]))
+    return n
+
+
+FORESTS = [([-1], [64 * n]) for n in (1, 4, 8, 12, 14, 16, 24, 31, 32, 64, 130, 300)] + [
+    ([-1, 0, 0, 1, 1], [1500, 700, 90, 640, 333]), ([-1] + [0] * 9, [130] + [70] * 9), ([-1, -1, 1], [65, 2000, 900])]
+
+
+def test_block_chunks_follow_from_the_counts(L):
+    """The block size of every round from the block counts alone: the largest
+    that reaches the default target, else the smallest of 4, 2, 1 with at most
+    256 (block, head) workgroups, each tried only while the one before it
+    fits, else 8."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    seen = set()
+    for heads in (1, 3, 4, 16, 40):
+        for parent, seg_len in FORESTS:
+            p = HartsPlan(parent, seg_len, 64, heads=heads)
+            for r, rd in enumerate(p.rounds):
+                want = next((c for c in (64, 48, 32, 24, 16, 12, 8) if count_blocks(p, r, c) >= -(-896 // heads)), 0)
+                if not want:
+                    want = 8
+                    for c in (4, 2, 1):
+                        if count_blocks(p, r, c) * heads > 256:
+                            break
+                        want = c
+                assert rd["block_chunks"] == want and rd["n_blk"] == count_blocks(p, r, want), (heads, seg_len, r)
+                seen.add(want)
+            p.close()
+    assert seen >= {1, 2, 4, 8}
+
+
+@pytest.mark.parametrize("heads", [1, 4, 16, 40])
+def test_short_blocks_refuse_no_call_that_8_chunk_blocks_take(L, heads):
+    """Whatever the heads of a call and those that its plan was cut for: the
+    scratch of a forward without saved states fits the 64 MiB of
+    harts_la_fwd_noalloc wherever 8-chunk blocks' does, and calls with more
+    than 256 (block, head) workgroups in short blocks need just what a plan
+    in 8-chunk blocks asks for, in every pass."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    sz = C.c_size_t()
+
+    def size(p, r, H, d, bwd, keep):
+        assert L.harts_la_workspace_size(p.handle, r, bwd, 1, H, d, d, keep, C.byref(sz)) == 0
+        return sz.value
+
+    short = fell_back = 0
+    for parent, seg_len in FORESTS:
+        p = HartsPlan(parent, seg_len, 64, heads=heads)
+        p8 = HartsPlan(parent, seg_len, 64, heads=heads, min_blocks=100000)
+        for r, rd in enumerate(p.rounds):
+            if rd["block_chunks"] >= 8:
+                continue
+            short += 1
+            for H in (1, 2, heads, 17, 32, 40, 64, 128, 1000):
+                for d in (64, 128):
+                    if size(p8, r, H, d, 0, 0) <= 64 << 20:
+                        assert size(p, r, H, d, 0, 0) <= 64 << 20, (seg_len, H, d)
+                    if rd["n_blk"] * H > 256:
+                        fell_back += 1
+                        for bwd in (0, 1):
+                            for keep in (0, 1):
+                                assert size(p, r, H, d, bwd, keep) == size(p8, r, H, d, bwd, keep)
+        p.close()
+        p8.close()
+    assert short > 5 and fell_back > 20

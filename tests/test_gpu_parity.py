@@ -254,3 +254,30 @@ def test_short_blocks_and_long_chains(dtype, d, H, recompute):
     r = np.random.default_rng(d + H)
     x = draw_inputs(int(np.sum(seg_len)), 4, H, d, d, r, dtype, n_trees=2, s0_scale=0.5)
     compare(parent, seg_len, x, H, d, dtype, recompute=recompute, label=f"short blocks {dtype} d{d} H{H}")
+
+
+@pytest.mark.parametrize("recompute", [False, True], ids=["saved", "recompute"])
+@pytest.mark.parametrize("d,H", [(64, 70), (128, 45)])
+def test_more_heads_than_the_plan_was_cut_for(d, H, recompute):
+    """A small plan cut for 16 heads (short blocks) and called with so many
+    that it takes its 8-chunk tables: every output has the bits of a plan that
+    is in 8-chunk blocks."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    from paper_2608_28158_amd.tree_la import TreeLARunner
+    parent, seg_len = [-1, 0, 0, 1, 1], [500, 300, 90, 340, 133]
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    n = sum(seg_len)
+    draw = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    q, k, v, dO = (draw(n, H, d).to(torch.bfloat16) * 0.3 for _ in range(4))
+    g, S0, dSf = -0.1 * torch.rand((n, H), device="cuda", generator=gen), draw(1, H, d, d), draw(3, H, d, d)
+    outs = []
+    for min_blocks in (0, 100000):
+        plan = HartsPlan(parent, seg_len, 64, min_blocks=min_blocks)
+        assert all((rd["block_chunks"] < 8) == (not min_blocks) for rd in plan.rounds)
+        assert min_blocks or all(rd["n_blk"] * H > 256 for rd in plan.rounds)
+        run = TreeLARunner(plan, H, d, torch.bfloat16, "cuda")
+        f = run.forward(q, k, v, g, S0, keep_states=not recompute)
+        b = run.backward(q, k, v, g, dO, dSf, fwd=f, recompute=recompute)
+        outs.append({**{x: f[x] for x in ("o", "S_final")}, **{x: b[x] for x in ("dq", "dk", "dv", "dg", "dS0_tree")}})
+    for x in outs[0]:
+        assert torch.isfinite(outs[0][x]).all() and torch.equal(outs[0][x], outs[1][x]), x

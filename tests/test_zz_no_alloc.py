@@ -92,6 +92,33 @@ def test_noalloc_forward_matches_workspace_forward(L):
         plan.close()
 
 
+@pytest.mark.parametrize("rows,H,d,dtype", [(1024, 16, 128, "bf16"), (1024, 64, 128, "bf16"), (2000, 40, 128, "bf16"),
+                                            (1500, 128, 64, "bf16"), (700, 4, 64, "f32")])
+def test_noalloc_forward_of_a_default_plan(L, rows, H, d, dtype):
+    """A plan as it comes (cut for 16 heads, short blocks), called with its own
+    number of heads and with others: the same bits as harts_la_fwd, and, where
+    the call has too many heads for short blocks, as a plan in 8-chunk blocks."""
+    from paper_2608_28158_amd import _lib
+    from paper_2608_28158_amd.plan import HartsPlan
+    parent, seg_len = [-1, 0, 0], [rows // 2, rows - rows // 2, 100]
+    plan = HartsPlan(parent, seg_len, 64)
+    assert all(rd["block_chunks"] < 8 for rd in plan.rounds)
+    wide = HartsPlan(parent, seg_len, 64, min_blocks=100000)
+    code = _lib.HARTS_F32 if dtype == "f32" else _lib.HARTS_BF16
+    x = draw_inputs(plan["C"], plan["n_leaves"], H, d, d, np.random.default_rng(rows + H), dtype,
+                    n_trees=plan["n_trees"], s0_scale=0.3)
+    a = forward_all_rounds(L, plan, plan.blob("cuda"), code, H, d, x, noalloc=False)
+    b = forward_all_rounds(L, plan, plan.blob("cuda"), code, H, d, x, noalloc=True)
+    c = forward_all_rounds(L, wide, wide.blob("cuda"), code, H, d, x, noalloc=False)
+    more = all(rd["n_blk"] * H > 256 for rd in plan.rounds)
+    for name in a:
+        assert np.isfinite(a[name]).all(), name
+        assert np.array_equal(a[name], b[name]), name
+        assert not more or np.array_equal(a[name], c[name]), name
+    plan.close()
+    wide.close()
+
+
 def test_noalloc_rejects_rounds_beyond_its_scratch(L):
     """A round whose scratch exceeds the fixed array is refused with
     HARTS_ENOMEM before anything is enqueued."""
