@@ -638,25 +638,21 @@ __global__ __launch_bounds__(SCAN_THR) void k_fwd_blockscan(
     reinterpret_cast<float4*>(S_end)[bi * SS4 + e4] = s;
     if (eb >= 0 && bank) reinterpret_cast<float4*>(bank)[(static_cast<int64_t>(eb) * H + h) * SS4 + e4] = s;
   };
-  // Whole batches: the next one is requested before this one's states are
-  // stored (loads and stores complete in order), past the last it again.  A
-  // chain of about 120 blocks took 43 us when every batch waited for the
-  // stores of the one before it and every block for its bank entry; now 15 us.
+  // A batch is requested before the states of the one before it are stored
+  // (loads and stores complete in order); the remainder with the last whole
+  // batch.  A chain of about 120 blocks took 43 us when every batch waited for
+  // the stores of the one before it and every block for its bank entry.
+  float4 x[SCAN_PF], xn[SCAN_PF];
+  float gm[SCAN_PF], gn[SCAN_PF];
+  int eb[SCAN_PF], en[SCAN_PF];
   int bg = b0;
-  const int b_full = b0 + nb / SCAN_PF * SCAN_PF;
-  if (bg < b_full) {
-    float4 x[SCAN_PF];
-    float gm[SCAN_PF];
-    int eb[SCAN_PF];
+  const int b_end = b0 + nb;
+  if (nb >= SCAN_PF) {
 #pragma unroll
     for (int i = 0; i < SCAN_PF; ++i) load(x[i], gm[i], eb[i], bg + i);
-    for (; bg < b_full; bg += SCAN_PF) {
-      float4 xn[SCAN_PF];
-      float gn[SCAN_PF];
-      int en[SCAN_PF];
-      const int nx = min(bg + SCAN_PF, b_full - SCAN_PF);
+    for (; bg + 2 * SCAN_PF <= b_end; bg += SCAN_PF) {
 #pragma unroll
-      for (int i = 0; i < SCAN_PF; ++i) load(xn[i], gn[i], en[i], nx + i);
+      for (int i = 0; i < SCAN_PF; ++i) load(xn[i], gn[i], en[i], bg + SCAN_PF + i);
 #pragma unroll
       for (int i = 0; i < SCAN_PF; ++i) step(x[i], gm[i], eb[i], bg + i);
 #pragma unroll
@@ -666,18 +662,20 @@ __global__ __launch_bounds__(SCAN_THR) void k_fwd_blockscan(
         eb[i] = en[i];
       }
     }
-  }
-  {
-    float4 x[SCAN_PF - 1];
-    float gm[SCAN_PF - 1];
-    int eb[SCAN_PF - 1];
 #pragma unroll
     for (int i = 0; i < SCAN_PF - 1; ++i)
-      if (bg + i < b0 + nb) load(x[i], gm[i], eb[i], bg + i);
+      if (bg + SCAN_PF + i < b_end) load(xn[i], gn[i], en[i], bg + SCAN_PF + i);
+#pragma unroll
+    for (int i = 0; i < SCAN_PF; ++i) step(x[i], gm[i], eb[i], bg + i);
+    bg += SCAN_PF;
+  } else {
 #pragma unroll
     for (int i = 0; i < SCAN_PF - 1; ++i)
-      if (bg + i < b0 + nb) step(x[i], gm[i], eb[i], bg + i);
+      if (bg + i < b_end) load(xn[i], gn[i], en[i], bg + i);
   }
+#pragma unroll
+  for (int i = 0; i < SCAN_PF - 1; ++i)
+    if (bg + i < b_end) step(xn[i], gn[i], en[i], bg + i);
   if (S_final && !skip1)
     reinterpret_cast<float4*>(S_final)[(static_cast<int64_t>(seq[SEQ_FINAL_LEAF]) * H + h) * SS4 + e4] = s;
 }
@@ -742,41 +740,18 @@ __global__ __launch_bounds__(SCAN_THR) void k_bwd_blockscan(
     if (t == 0) betap[pi * NSW + part] = bsum;
     reinterpret_cast<float4*>(dS_end)[pi * SS4 + e4] = ds;
   };
-  // blocks b0 + nb - 1 down to b0 + 1, in batches as in the forward
+  // blocks b0 + nb - 1 down to b0 + 1, in batches (requested ahead of the
+  // stores as in the forward, they measured the same)
   int bg = b0 + nb - 1;
-  const int b_full = bg - (nb - 1) / SCAN_PF * SCAN_PF;   // whole batches cover (b_full, bg]
-  if (bg > b_full) {
+  for (; bg > b0; bg -= SCAN_PF) {
     float4 u[SCAN_PF];
     float gm[SCAN_PF];
     int eb[SCAN_PF];
 #pragma unroll
-    for (int i = 0; i < SCAN_PF; ++i) load(u[i], gm[i], eb[i], bg - i);
-    for (; bg > b_full; bg -= SCAN_PF) {
-      float4 un[SCAN_PF];
-      float gn[SCAN_PF];
-      int en[SCAN_PF];
-      const int nx = max(bg - SCAN_PF, b_full + SCAN_PF);
-#pragma unroll
-      for (int i = 0; i < SCAN_PF; ++i) load(un[i], gn[i], en[i], nx - i);
-#pragma unroll
-      for (int i = 0; i < SCAN_PF; ++i) step(u[i], gm[i], eb[i], bg - i);
-#pragma unroll
-      for (int i = 0; i < SCAN_PF; ++i) {
-        u[i] = un[i];
-        gm[i] = gn[i];
-        eb[i] = en[i];
-      }
-    }
-  }
-  {
-    float4 u[SCAN_PF - 1];
-    float gm[SCAN_PF - 1];
-    int eb[SCAN_PF - 1];
-#pragma unroll
-    for (int i = 0; i < SCAN_PF - 1; ++i)
+    for (int i = 0; i < SCAN_PF; ++i)
       if (bg - i > b0) load(u[i], gm[i], eb[i], bg - i);
 #pragma unroll
-    for (int i = 0; i < SCAN_PF - 1; ++i)
+    for (int i = 0; i < SCAN_PF; ++i)
       if (bg - i > b0) step(u[i], gm[i], eb[i], bg - i);
   }
 }
