@@ -294,11 +294,18 @@ int check_logits(int32_t dtype, int64_t C, int64_t V, const char* where) {
   return HARTS_OK;
 }
 
+// Rows of a grid of one workgroup each: a launch holds fewer than 2^32 threads,
+// so from 2^22 rows on long ones take 256 threads as well.
+template <typename T>
+bool wide_rows(int64_t C, int64_t V) {
+  return V / LV<T>::N >= LP_WIDE && C < (int64_t{1} << 32) / LP_THR_W;
+}
+
 template <typename T>
 int launch_lse(int64_t C, int64_t V, const void* z, float* lse, hipStream_t s) {
   const dim3 grid(static_cast<uint32_t>(C));
   const T* zz = static_cast<const T*>(z);
-  const bool wide = V / LV<T>::N >= LP_WIDE;
+  const bool wide = wide_rows<T>(C, V);
   if (C > LP_STREAM / static_cast<int64_t>(sizeof(T)) / V) {
     if (wide) hipLaunchKernelGGL((k_logp_lse<T, LP_THR_W, true>), grid, dim3(LP_THR_W), 0, s, zz, V, lse);
     else hipLaunchKernelGGL((k_logp_lse<T, LP_THR, true>), grid, dim3(LP_THR), 0, s, zz, V, lse);
@@ -320,7 +327,7 @@ void launch_grad_as(int64_t C, int64_t V, const void* z, const float* lse, const
 template <typename T>
 int launch_grad(int64_t C, int64_t V, const void* z, const float* lse, const int64_t* row_off, const int32_t* row_pos,
                 const int32_t* y, const float* g, int64_t n_pos, float* G, void* dz, hipStream_t s) {
-  const bool wide = V / LV<T>::N >= LP_WIDE;
+  const bool wide = wide_rows<T>(C, V);
   const auto f = C > LP_STREAM / static_cast<int64_t>(sizeof(T)) / V
                      ? (wide ? launch_grad_as<T, LP_THR_W, true> : launch_grad_as<T, LP_THR, true>)
                      : (wide ? launch_grad_as<T, LP_THR_W, false> : launch_grad_as<T, LP_THR, false>);

@@ -258,3 +258,25 @@ def test_logp_nan_logits_of_rows_without_gradient(L, V, dtype):
     rest = dz[1:5].masked_fill(bad[1:5], 0)
     rest[3, 7] = rest[3, 9] = 0         # the targets whose gradients cancel over the row
     assert not rest.any() and not row_g[1:5].any()
+
+
+def test_logp_more_rows_than_wide_workgroups(L):
+    """2^22 long rows, one more than a launch of 1,024 threads a row can hold
+    (137 GB of float32 logits): the log-sum-exp of every row.  All logits of a
+    row are one value, so it is that value plus log V."""
+    from paper_2608_28158_amd import _lib
+    Cn, V = 1 << 22, 8192
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < Cn * V * 4 + (8 << 30):
+        pytest.skip("not enough device memory")
+    z = torch.empty((Cn, V), dtype=torch.float32, device="cuda")
+    val = (torch.arange(Cn, device="cuda") % 251).float() / 16
+    z.copy_(val[:, None].expand(Cn, V))
+    lse = torch.full((Cn,), float("nan"), device="cuda")
+    null = C.c_void_p()
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    _lib.check(L.harts_logp_fwd(_lib.HARTS_F32, Cn, V, _p(z), 0, null, null, _p(lse), null, st), "harts_logp_fwd")
+    # a sum of 8,192 equal terms, a float32 logarithm: below 1e-5 of about 20
+    assert float((lse - (val + np.log(V))).abs().max()) < 2e-4
+    del z
+    torch.cuda.empty_cache()
