@@ -6,12 +6,17 @@
 // the workgroup's LDS (16 bits of M0) and is the same for the whole wave.
 //
 // Written as asm because the compiler lets every LDS read wait for a load of
-// this kind.  Nothing else in the kernels that use it may use M0.
+// this kind.  M0 is declared as overwritten, so that an M0 of the compiler's
+// own would be set again after it (there is none in the kernels now); it warns
+// that the register is one of its reserved ones.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 
 namespace harts {
 
@@ -27,7 +32,7 @@ __device__ inline void lds_load16(const void* base, uint32_t off, const T* dst) 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
                : "s"(lds_base(dst)), "v"(off), "s"(base)
-               : "memory");
+               : "m0", "memory");
 }
 
 // from each lane's own address
@@ -36,7 +41,7 @@ __device__ inline void lds_load16(const void* p, const T* dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :
                : "s"(lds_base(dst)), "v"(p)
-               : "memory");
+               : "m0", "memory");
 }
 
 // Every load of this wave has landed (vmcnt 0; the builtin also tells the
@@ -49,3 +54,5 @@ __device__ inline void lds_landed() {
 }
 
 }  // namespace harts
+
+#pragma clang diagnostic pop
