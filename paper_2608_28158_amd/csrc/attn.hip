@@ -279,9 +279,11 @@ __global__ __launch_bounds__(AT_THR, NH == 2 ? 3 : 2) void k_attn_fwd(const int3
     }
     // online softmax in base 2 against a reference maximum m per row: it is
     // raised (and the accumulators rescaled) only when some score of the
-    // wave exceeds its row's m by more than the slack
+    // wave exceeds its row's m by more than the slack, and until it is the
+    // maximum of the first 64 keys: of 32 it is less often the row's own, whose
+    // weight, the heaviest, then is 1 and not rounded to bf16
     float tmx[NH];
-    bool raise = false;
+    bool raise = T < 64 && k0 == T;
 #pragma unroll
     for (int a = 0; a < NH; ++a) {
       float x = sc[a][0][0];

@@ -304,3 +304,30 @@ def test_attn_bwd_dq_over_o(L, d, H, shift):
     a, b = outs[0][0], outs[1][0]
     assert float((a - b).abs().max()) <= 2.0 ** -7 * float(a.abs().max())
     assert float((a - b).norm()) <= 2.0 ** -10 * float(a.norm())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [2, 512], ids=["64-row workgroups", "128-row workgroups"])
+@pytest.mark.parametrize("key", [20, 40])
+def test_attn_heaviest_weight_of_the_first_keys_is_exact(L, d, H, key):
+    """Weights are rounded to bf16 against a reference that is the maximum of
+    a row's first 64 keys: the heaviest of those has the weight 1 and no
+    rounding error.  One key's score is 3.005 (base 2) above all others', whose
+    values are zero; rounded against the others' score its weight would be 8
+    for 8.028, and every output 3.5e-3 too small."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    plan = HartsPlan([-1], [128], 64)
+    gen = torch.Generator(device="cuda").manual_seed(key)
+    q, k, v = (torch.zeros((128, H, d), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    q[:, :, 0], k[key, :, 0] = 1.0, 23.5
+    q[:, :, 1], k[key, :, 1] = 1.0, 0.0664
+    v[key] = torch.randn((H, d), device="cuda", generator=gen).to(torch.bfloat16)
+    scale = 128 ** -0.5
+    o = run_attn(L, plan, q, k, v, torch.zeros_like(q), H, d, scale)["o"].double()
+    assert int(plan["seg_row"][0]) == 0
+    w = 2.0 ** (float((q[0, 0].double() * k[key, 0].double()).sum()) * scale * np.log2(np.e))
+    assert w / 8 - 1 > 3.2e-3 and w / 8 < 1 + 2.0 ** -8
+    rows = torch.arange(key, 128, device="cuda")
+    ref = (w / (w + rows.double()))[:, None, None] * v[key].double()
+    # the outputs' own rounding (2^-9) averages out over the values
+    assert abs(float((o[rows] * ref).sum() / (ref * ref).sum()) - 1) < 2.0 ** -11
