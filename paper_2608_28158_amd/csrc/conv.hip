@@ -39,11 +39,13 @@ constexpr int CV_RT = 16;                     // rows of a sub-run
 constexpr int CV_RUN = CV_SUB * CV_RT;        // rows of a run (one partial dW per run)
 constexpr int CV_G = 4;                       // rows taken at a time
 constexpr int CV_SUCC = 1024;                 // consumer entries of a run staged in LDS
-static_assert(CV_SUB * 64 == CV_THR && CV_RUN == 64 && CV_RT % CV_G == 0, "one wave per sub-run, one lane per row");
+static_assert(CV_SUB * 64 == CV_THR && CV_RUN == 64 && CV_RT % CV_G == 0 && CV_RT <= 32, "one wave per sub-run, one bit per row");
 
 template <typename T> struct CV;
 template <> struct CV<bf16> {
   static constexpr int N = 4;  // 8-byte pieces: half the registers of 16-byte ones
+  static constexpr int B = 4;  // consumer entries of a row taken at a time (as many as the registers hold)
+  static constexpr int waves(int w) { return w <= 3 ? 4 : (w == 4 ? 3 : 2); }  // a SIMD, in the backward
   using Raw = uint2;           // a piece as loaded, widened where it is used
   __device__ static inline Raw raw(const bf16* p) { return *reinterpret_cast<const uint2*>(p); }
   __device__ static inline void cvt(const Raw u, float* x) {
@@ -63,6 +65,8 @@ template <> struct CV<bf16> {
 };
 template <> struct CV<float> {
   static constexpr int N = 4;
+  static constexpr int B = 2;
+  static constexpr int waves(int w) { return w == 2 ? 4 : (w <= 4 ? 3 : 2); }
   using Raw = float4;
   __device__ static inline Raw raw(const float* p) { return *reinterpret_cast<const float4*>(p); }
   __device__ static inline void cvt(const Raw u, float* x) {
@@ -87,12 +91,20 @@ template <> struct CV<float> {
 // rows: 544 and 22.3 us, of 8 rows: 809 and 17.6; two rows at a time: 597 and
 // 15.2 us.
 //
-// A row is regular when its predecessors are the rows just above it and, in
-// the backward, its consumers exactly the rows just below it: all rows of a
-// segment but the first and last W - 1.  Rows are taken CV_G at a time; a
-// group of regular rows needs no tables and no branches, its windows over x
-// and dy stay in registers.  Any other group takes its rows one by one, every
-// tap and consumer through the tables.  Both add in the same order.
+// The windows over x and dy stay in registers.  A row whose predecessors are
+// the row above it and that row's own needs no table, whatever segments they
+// lie in: the window moves by one.  At any other row (in the forests of trees:
+// a segment's first) the window is gathered through the table, its W - 1 loads
+// together.  In the backward a row whose consumers are exactly the W - 1 rows
+// below it needs no table either; any other row takes its consumers in table
+// order, those in the window from registers, the rest a few requests at a
+// time.  Groups of CV_G rows without either have no branches.  Every row adds
+// in the same order on every path.  With every tap and consumer of a segment's
+// first and last W - 1 rows loaded one by one, forests of short segments took
+// up to three times as long: 65,536 x 6,144 bf16, forward and backward, w = 4:
+// segments of 1 to 200 rows 307 + 630 -> 310 + 532 us, of 8 371 + 1,276 -> 317
+// + 737, of 3 570 + 1,779 -> 333 + 1,016; w = 8, of 1 to 200 rows 489 + 2,552
+// -> 346 + 1,011 us.
 template <typename T, int W>
 __device__ inline void load_taps(const float* __restrict__ Wt, int c0, float (&wt)[W][CV<T>::N]) {
 #pragma unroll
@@ -111,18 +123,6 @@ __device__ inline void load_taps(const float* __restrict__ Wt, int c0, float (&w
   }
 }
 
-// v <- x[p] (zero before the trajectory start or for an invalid entry)
-template <typename T>
-__device__ inline void load_row(const T* __restrict__ x, int64_t C, int Cch, int c0, int32_t p,
-                                float (&v)[CV<T>::N]) {
-  if (p >= 0 && p < C) {
-    CV<T>::load(x + static_cast<int64_t>(p) * Cch + c0, v);
-  } else {
-#pragma unroll
-    for (int e = 0; e < CV<T>::N; ++e) v[e] = 0.f;
-  }
-}
-
 // The row's predecessors are the W - 1 rows just above it.
 template <int W>
 __device__ inline bool regular_pred(const int32_t* pr, int64_t r) {
@@ -132,16 +132,40 @@ __device__ inline bool regular_pred(const int32_t* pr, int64_t r) {
   return ok;
 }
 
-// Bit g of the result: rows CV_G g .. CV_G g + CV_G - 1 of the sub-run (first
-// row f of the run, n rows) are all in the run's mask of regular rows.
-__device__ inline uint32_t regular_groups(unsigned long long rows, int f, int n) {
-  uint32_t m = 0;
+// Bit i of the result: row rs + i of a wave's sub-run (n rows, their table
+// entries at pr) does not follow from the row above it, i.e. its predecessors
+// are not that row and then that row's own (at the sub-run's first row: not
+// the W - 1 rows just above it, which the window starts with).
+template <int W>
+__device__ inline uint32_t window_breaks(const int32_t* pr, int64_t rs, int n, int lane) {
+  bool brk = false;
+  if (lane < n) {
+    const int32_t* p = pr + lane * (W - 1);
+    if (lane == 0) {
+      brk = !regular_pred<W>(p, rs);
+    } else {
+      brk = p[0] != rs + lane - 1;
 #pragma unroll
-  for (int g = 0; g < CV_RT / CV_G; ++g) {
-    const uint32_t four = static_cast<uint32_t>(rows >> (f + CV_G * g)) & ((1u << CV_G) - 1u);
-    m |= (four == (1u << CV_G) - 1u && CV_G * (g + 1) <= n ? 1u : 0u) << g;
+      for (int i = 2; i < W; ++i) brk |= p[i - 1] != p[i - 2 - (W - 1)];
+    }
   }
-  return __builtin_amdgcn_readfirstlane(m);
+  return static_cast<uint32_t>(__ballot(brk));
+}
+
+// The window over x at a break: xw[-i] <- x[pred_i] (zero before the trajectory
+// start or for an invalid entry), all of them requested together.
+template <typename T, int W>
+__device__ inline void gather_window(typename CV<T>::Raw* xw, const T* __restrict__ x, int64_t C, int Cch, int c0,
+                                     const int32_t* pr) {
+  int32_t p[W - 1];
+#pragma unroll
+  for (int i = 1; i < W; ++i) p[i - 1] = __builtin_amdgcn_readfirstlane(pr[i - 1]);
+#pragma unroll
+  for (int i = 1; i < W; ++i)
+    xw[-i] = CV<T>::raw(x + (p[i - 1] >= 0 && p[i - 1] < C ? static_cast<int64_t>(p[i - 1]) : 0) * Cch + c0);
+#pragma unroll
+  for (int i = 1; i < W; ++i)
+    if (!(p[i - 1] >= 0 && p[i - 1] < C)) xw[-i] = typename CV<T>::Raw{};
 }
 
 template <typename T, int W>
@@ -150,7 +174,7 @@ __global__ __launch_bounds__(CV_THR) void k_conv_fwd(int64_t C, int Cch, const T
                                                      const int32_t* __restrict__ pred, T* __restrict__ y) {
   using V = CV<T>;
   using Raw = typename V::Raw;
-  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int vec = blockIdx.x * 64 + lane;
   const int c0 = vec * V::N;
   const int64_t r0 = static_cast<int64_t>(blockIdx.y) * CV_RUN;
@@ -160,16 +184,16 @@ __global__ __launch_bounds__(CV_THR) void k_conv_fwd(int64_t C, int Cch, const T
   __shared__ int32_t s_pred[CV_RUN * (W - 1)];
   for (int j = threadIdx.x; j < (r1 - r0) * (W - 1); j += CV_THR) s_pred[j] = pred[r0 * (W - 1) + j];
   __syncthreads();
-  const unsigned long long rows =
-      __ballot(r0 + lane < r1 && regular_pred<W>(s_pred + lane * (W - 1), r0 + lane));
   const int64_t rs = r0 + sub * CV_RT;
   const int n = static_cast<int>(r1 - rs < CV_RT ? r1 - rs : CV_RT);
-  if (vec >= Cch / V::N || n <= 0) return;
-  const uint32_t fast = regular_groups(rows, sub * CV_RT, n);
+  if (n <= 0) return;
+  const int32_t* sp = s_pred + sub * CV_RT * (W - 1);
+  const uint32_t brk = window_breaks<W>(sp, rs, n, lane);
+  if (vec >= Cch / V::N) return;
   float wt[W][V::N];
   load_taps<T, W>(Wt, c0, wt);
   // xw[j] = x[row - (W - 1) + j] as loaded; requests past either end are
-  // clamped and never used (a regular row's window lies inside the tensor)
+  // clamped and never used (a window that reaches past the start is gathered)
   Raw xw[W - 1 + CV_G];
 #pragma unroll
   for (int j = 0; j < W - 1 + CV_G; ++j) {
@@ -184,35 +208,29 @@ __global__ __launch_bounds__(CV_THR) void k_conv_fwd(int64_t C, int Cch, const T
 #pragma unroll
     for (int q = 0; q < CV_G; ++q)
       if (CV_G * (g + 1) < n) xn[q] = V::raw(x + (r + CV_G + q < C ? r + CV_G + q : C - 1) * Cch + c0);
-    if (fast >> g & 1u) {
+    const auto row = [&](int q) __attribute__((always_inline)) {
+      float v[V::N], acc[V::N];
+      V::cvt(xw[W - 1 + q], v);
+#pragma unroll
+      for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * v[e];
+#pragma unroll
+      for (int i = 1; i < W; ++i) {
+        V::cvt(xw[W - 1 + q - i], v);
+#pragma unroll
+        for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
+      }
+      V::store(y + (r + q) * Cch + c0, acc);
+    };
+    const uint32_t gb = brk >> (CV_G * g) & ((1u << CV_G) - 1u);
+    if (gb == 0 && CV_G * (g + 1) <= n) {
+#pragma unroll
+      for (int q = 0; q < CV_G; ++q) row(q);
+    } else {
 #pragma unroll
       for (int q = 0; q < CV_G; ++q) {
-        float v[V::N], acc[V::N];
-        V::cvt(xw[W - 1 + q], v);
-#pragma unroll
-        for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * v[e];
-#pragma unroll
-        for (int i = 1; i < W; ++i) {
-          V::cvt(xw[W - 1 + q - i], v);
-#pragma unroll
-          for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
-        }
-        V::store(y + (r + q) * Cch + c0, acc);
-      }
-    } else {
-      const int64_t re = r + CV_G < rs + n ? r + CV_G : rs + n;
-      for (int64_t rr = r; rr < re; ++rr) {
-        float v[V::N], acc[V::N];
-        V::load(x + rr * Cch + c0, v);
-#pragma unroll
-        for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * v[e];
-#pragma unroll
-        for (int i = 1; i < W; ++i) {
-          load_row<T>(x, C, Cch, c0, s_pred[(rr - r0) * (W - 1) + i - 1], v);
-#pragma unroll
-          for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
-        }
-        V::store(y + rr * Cch + c0, acc);
+        if (CV_G * g + q >= n) break;
+        if (gb >> q & 1u) gather_window<T, W>(xw + W - 1 + q, x, C, Cch, c0, sp + (CV_G * g + q) * (W - 1));
+        row(q);
       }
     }
 #pragma unroll
@@ -225,7 +243,7 @@ __global__ __launch_bounds__(CV_THR) void k_conv_fwd(int64_t C, int Cch, const T
 // dx of a run of rows, and the run's partial weight gradient:
 // part[run][i][c] = sum over the run's rows r of x[pred_i(r)][c] dy[r][c].
 template <typename T, int W>
-__global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T* __restrict__ x,
+__global__ __launch_bounds__(CV_THR, CV<T>::waves(W)) void k_conv_bwd(int64_t C, int Cch, const T* __restrict__ x,
                                                      const float* __restrict__ Wt,
                                                      const int32_t* __restrict__ pred,
                                                      const int64_t* __restrict__ succ_off,
@@ -234,7 +252,7 @@ __global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T
                                                      float* __restrict__ part) {
   using V = CV<T>;
   using Raw = typename V::Raw;
-  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int vec = blockIdx.x * 64 + lane;
   const int c0 = vec * V::N;
   const int64_t r0 = static_cast<int64_t>(blockIdx.y) * CV_RUN;
@@ -259,33 +277,34 @@ __global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T
   const int32_t n_run_succ = s_off[nr];
   for (int j = threadIdx.x; j < n_run_succ && j < CV_SUCC; j += CV_THR) s_succ[j] = succ[b0 + j];
   __syncthreads();
-  bool reg = false;
-  if (lane < nr) {
-    const int64_t r = r0 + lane;
-    const int32_t jb = s_off[lane];
-    reg = regular_pred<W>(s_pred + lane * (W - 1), r) && r + W - 1 < C && s_off[lane + 1] == jb + W - 1 &&
-          jb + W - 1 <= CV_SUCC;
-    if (reg) {
-#pragma unroll
-      for (int i = 1; i < W; ++i) reg &= s_succ[jb + i - 1] == (r + i) * 8 + i;
-    }
-  }
-  const unsigned long long rows = __ballot(reg);
   const int64_t rs = r0 + sub * CV_RT;
   const int n = static_cast<int>(r1 - rs < CV_RT ? r1 - rs : CV_RT);
   const bool live = vec < Cch / V::N;
+  const int32_t* sp = s_pred + sub * CV_RT * (W - 1);
+  const uint32_t brk = window_breaks<W>(sp, rs, n, lane);
+  // rows whose consumers are not exactly the W - 1 rows just below them
+  bool far = false;
+  if (lane < n) {
+    const int64_t r = rs + lane;
+    const int32_t jb = s_off[sub * CV_RT + lane];
+    far = r + W - 1 >= C || s_off[sub * CV_RT + lane + 1] != jb + W - 1 || jb + W - 1 > CV_SUCC;
+    if (!far) {
+#pragma unroll
+      for (int i = 1; i < W; ++i) far |= s_succ[jb + i - 1] != (r + i) * 8 + i;
+    }
+  }
+  const uint32_t fars = static_cast<uint32_t>(__ballot(far));
   float gw[W][V::N];
 #pragma unroll
   for (int i = 0; i < W; ++i)
 #pragma unroll
     for (int e = 0; e < V::N; ++e) gw[i][e] = 0.f;
   if (live && n > 0) {
-    const uint32_t fast = regular_groups(rows, sub * CV_RT, n);
     float wt[W][V::N];
     load_taps<T, W>(Wt, c0, wt);
     // windows as loaded: xw[j] = x[row - (W - 1) + j], dw[j] = dy[row + j];
-    // requests past either end are clamped and never used (a regular row's
-    // windows lie inside the tensors)
+    // requests past either end are clamped and never used (a window over x
+    // that reaches past the start is gathered, no consumer is past the end)
     Raw xw[W - 1 + CV_G], dw[W - 1 + CV_G];
 #pragma unroll
     for (int j = 0; j < W - 1 + CV_G; ++j) {
@@ -302,62 +321,85 @@ __global__ __launch_bounds__(CV_THR) void k_conv_bwd(int64_t C, int Cch, const T
         xn[q] = V::raw(x + (rx < C ? rx : C - 1) * Cch + c0);
         dn[q] = V::raw(dy + (rd < C ? rd : C - 1) * Cch + c0);
       }
-      if (fast >> g & 1u) {
+      // the row's tap sums and its own term of dx
+      const auto own = [&](int q, float (&acc)[V::N]) __attribute__((always_inline)) {
+        float d0[V::N], v[V::N];
+        V::cvt(dw[q], d0);
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+          V::cvt(xw[W - 1 + q - i], v);
+#pragma unroll
+          for (int e = 0; e < V::N; ++e) gw[i][e] += v[e] * d0[e];
+        }
+#pragma unroll
+        for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * d0[e];
+      };
+      // the terms of the W - 1 rows below
+      const auto below = [&](int q, float (&acc)[V::N]) __attribute__((always_inline)) {
+        float v[V::N];
+#pragma unroll
+        for (int i = 1; i < W; ++i) {
+          V::cvt(dw[q + i], v);
+#pragma unroll
+          for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
+        }
+      };
+      const uint32_t gb = brk >> (CV_G * g) & ((1u << CV_G) - 1u);
+      const uint32_t gf = fars >> (CV_G * g) & ((1u << CV_G) - 1u);
+      if ((gb | gf) == 0 && CV_G * (g + 1) <= n) {
 #pragma unroll
         for (int q = 0; q < CV_G; ++q) {
-          float d0[V::N], v[V::N], acc[V::N];
-          V::cvt(dw[q], d0);
-#pragma unroll
-          for (int i = 0; i < W; ++i) {
-            V::cvt(xw[W - 1 + q - i], v);
-#pragma unroll
-            for (int e = 0; e < V::N; ++e) gw[i][e] += v[e] * d0[e];
-          }
-#pragma unroll
-          for (int e = 0; e < V::N; ++e) acc[e] = wt[0][e] * d0[e];
-#pragma unroll
-          for (int i = 1; i < W; ++i) {
-            V::cvt(dw[q + i], v);
-#pragma unroll
-            for (int e = 0; e < V::N; ++e) acc[e] += wt[i][e] * v[e];
-          }
+          float acc[V::N];
+          own(q, acc);
+          below(q, acc);
           V::store(dx + (r + q) * Cch + c0, acc);
         }
       } else {
-        const int64_t re = r + CV_G < rs + n ? r + CV_G : rs + n;
-        for (int64_t rr = r; rr < re; ++rr) {
-          float d0[V::N], v[V::N], acc[V::N];
-          V::load(dy + rr * Cch + c0, d0);
-          V::load(x + rr * Cch + c0, v);
 #pragma unroll
-          for (int e = 0; e < V::N; ++e) {
-            acc[e] = wt[0][e] * d0[e];
-            gw[0][e] += v[e] * d0[e];
-          }
+        for (int q = 0; q < CV_G; ++q) {
+          const int lr = CV_G * g + q;   // row of the sub-run
+          if (lr >= n) break;
+          if (gb >> q & 1u) gather_window<T, W>(xw + W - 1 + q, x, C, Cch, c0, sp + lr * (W - 1));
+          float acc[V::N];
+          own(q, acc);
+          if (!(gf >> q & 1u)) {
+            below(q, acc);
+          } else {
+            // consumers in table order, V::B at a time: the staged entries
+            // from LDS, any beyond them from global memory (two loops, so that
+            // neither read goes through a flat address, which would wait for
+            // every outstanding load)
+            const auto consume = [&](int32_t j, int32_t je, auto entry) __attribute__((always_inline)) {
+              Raw rb[V::B];
+              int tap[V::B];      // 0: none
+              bool low[V::B];     // the row tap below: in the window
 #pragma unroll
-          for (int i = 1; i < W; ++i) {
-            load_row<T>(x, C, Cch, c0, s_pred[(rr - r0) * (W - 1) + i - 1], v);
-#pragma unroll
-            for (int e = 0; e < V::N; ++e) gw[i][e] += v[e] * d0[e];
-          }
-          // consumers in table order: the staged entries from LDS, any
-          // beyond them from global memory
-          const int32_t jb = s_off[rr - r0], je = s_off[rr - r0 + 1];
-          for (int32_t j = jb; j < je; ++j) {
-            int32_t code;
-            if (j < CV_SUCC) code = s_succ[j];
-            else code = succ[b0 + j];
-            const int32_t sr = code >> 3, i = code & 7;  // consumer row, tap
-            if (sr < 0 || sr >= C || i < 1 || i >= W) continue;
-            V::load(dy + static_cast<int64_t>(sr) * Cch + c0, v);
-#pragma unroll
-            for (int k = 1; k < W; ++k)
-              if (k == i) {
-#pragma unroll
-                for (int e = 0; e < V::N; ++e) acc[e] += wt[k][e] * v[e];
+              for (int u = 0; u < V::B; ++u) {
+                const int32_t code = j + u < je ? __builtin_amdgcn_readfirstlane(entry(j + u)) : -1;
+                const int32_t sr = code >> 3, i = code & 7;  // consumer row, tap
+                tap[u] = sr < 0 || sr >= C || i < 1 || i >= W ? 0 : i;
+                low[u] = sr == r + q + i;
+                if (tap[u] != 0 && !low[u]) rb[u] = V::raw(dy + static_cast<int64_t>(sr) * Cch + c0);
               }
+#pragma unroll
+              for (int u = 0; u < V::B; ++u)
+#pragma unroll
+                for (int k = 1; k < W; ++k)
+                  if (tap[u] == k) {
+                    float v[V::N];
+                    V::cvt(low[u] ? dw[q + k] : rb[u], v);
+#pragma unroll
+                    for (int e = 0; e < V::N; ++e) acc[e] += wt[k][e] * v[e];
+                  }
+            };
+            const int32_t jb = __builtin_amdgcn_readfirstlane(s_off[sub * CV_RT + lr]);
+            const int32_t je = __builtin_amdgcn_readfirstlane(s_off[sub * CV_RT + lr + 1]);
+            const int32_t jl = je < CV_SUCC ? je : CV_SUCC;
+            for (int32_t j = jb; j < jl; j += V::B) consume(j, jl, [&](int32_t k) { return s_succ[k]; });
+            for (int32_t j = jb > CV_SUCC ? jb : CV_SUCC; j < je; j += V::B)
+              consume(j, je, [&](int32_t k) { return succ[b0 + k]; });
           }
-          V::store(dx + rr * Cch + c0, acc);
+          V::store(dx + (r + q) * Cch + c0, acc);
         }
       }
 #pragma unroll

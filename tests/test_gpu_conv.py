@@ -152,6 +152,56 @@ def test_conv_run_edges(L, label, parent, seg_len, Cch, w, dtype):
     assert all(e <= TOL[dtype] for e in errs.values()), errs
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("w", [2, 3, 5, 8])
+def test_conv_any_tables(L, w, dtype):
+    """The kernels go by the tables alone: pieces that follow the row above,
+    jumps inside them, taps that break off one by one, entries before the start
+    and outside the tensor, consumers in any number and order with taps that
+    do not exist, against float64 sums over the same tables."""
+    from paper_2608_28158_amd import _lib
+    Cn, Cch, tdt = 333, 24, torch.float32 if dtype == "f32" else torch.bfloat16
+    code = _lib.HARTS_F32 if dtype == "f32" else _lib.HARTS_BF16
+    r = np.random.default_rng(w)
+    pred = np.full((Cn, w - 1), -1, np.int64)
+    for row in range(1, Cn):
+        pred[row, 0] = row - 1 if r.random() < 0.8 else r.integers(-2, Cn + 3)
+        for i in range(1, w - 1):
+            pred[row, i] = pred[row - 1, i - 1] if r.random() < 0.95 else r.integers(-2, Cn + 3)
+    lists = []
+    for row in range(Cn):
+        below = [(row + i) * 8 + i for i in range(1, w) if row + i < Cn]
+        kind = r.integers(0, 4)
+        more = list(r.integers(-8, 8 * Cn + 16, int(r.integers(1, 12))))
+        lists.append(below if kind < 2 else (below[:-1] + more if kind == 2 else more))
+    lists[100] = list(r.integers(0, 8 * Cn, 1500))      # more than a run stages
+    off = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    succ = np.concatenate([np.asarray(x, np.int64) for x in lists])
+    gen = torch.Generator(device="cuda").manual_seed(w)
+    x, dy = (torch.randn((Cn, Cch), device="cuda", generator=gen).to(tdt) for _ in range(2))
+    W = torch.randn((Cch, w), device="cuda", generator=gen)
+    pd, od, sd = (torch.from_numpy(a).cuda() for a in (pred.astype(np.int32), off, succ.astype(np.int32)))
+    y, dx, dW = torch.empty_like(x), torch.empty_like(x), torch.empty_like(W)
+    sz = C.c_size_t()
+    _lib.check(L.harts_conv_workspace_size(Cn, Cch, w, C.byref(sz)), "harts_conv_workspace_size")
+    ws = torch.empty(sz.value, dtype=torch.uint8, device="cuda")
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    _lib.check(L.harts_conv_fwd(code, Cn, Cch, w, _p(x), _p(W), _p(pd), _p(y), st), "harts_conv_fwd")
+    _lib.check(L.harts_conv_bwd(code, Cn, Cch, w, _p(x), _p(W), _p(pd), _p(od), _p(sd), len(succ), _p(dy), _p(dx),
+                                _p(dW), _p(ws), ws.numel(), st), "harts_conv_bwd")
+    xs, ds, Ws = (t.double().cpu().numpy() for t in (x, dy, W))
+    taps = [xs] + [np.where(((p >= 0) & (p < Cn))[:, None], xs[np.clip(p, 0, Cn - 1)], 0) for p in pred.T]
+    dx_ref = Ws[:, 0] * ds
+    for row, entries in enumerate(lists):
+        for e in entries:
+            if 0 <= e < 8 * Cn and 1 <= e % 8 < w:
+                dx_ref[row] += Ws[:, e % 8] * ds[e // 8]
+    errs = {"y": max_rel(y.float().cpu().numpy(), sum(Ws[:, i] * taps[i] for i in range(w))),
+            "dx": max_rel(dx.float().cpu().numpy(), dx_ref),
+            "dW": max_rel(dW.cpu().numpy(), np.stack([(t * ds).sum(0) for t in taps], 1))}
+    assert all(e <= TOL[dtype] for e in errs.values()), errs
+
+
 def test_conv_64k_workload_6144_channels_sampled(L):
     from paper_2608_28158_amd.plan import HartsPlan
     f, _, cfg = forest_for_config(2)
