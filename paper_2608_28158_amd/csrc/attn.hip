@@ -100,10 +100,11 @@ struct AtTile {
   }
 };
 
-// Rows row0 .. row0 + NR - 1 (clamped to the first n) of head h of a
-// [rows, H, D] tensor, requested straight into an LDS tile (lds_load.hpp):
+// Rows row0 .. row0 + NR - 1 of head h of a [rows, H, D] tensor (the first n of
+// them, zeros past those), requested straight into an LDS tile (lds_load.hpp):
 // the 16-byte pieces of a wave's request land in consecutive LDS slots, so the
-// lane picks the piece that belongs there.
+// lane picks the piece that belongs there.  (Zeros, because a masked weight is
+// 0 and 0 times another row's infinity would not be.)
 template <int D>
 struct AtRequest {
   static constexpr int PPR = AtTile<D>::PPR;
@@ -128,10 +129,21 @@ struct AtRequest {
       for (int e = 0; e < NR / RPE; ++e)
         lds_load16(base + e * RPE * static_cast<int64_t>(rowb), off, tile + (e * AT_THR + 64 * w) * 8);
     } else {
+      // (the zeros in 8-byte pieces take 6 registers fewer, which at d = 64
+      // keep the forward at four waves a SIMD; rolled, the loop cost 1% of a
+      // 2,000-row pass)
 #pragma unroll
-      for (int e = 0; e < NR / RPE; ++e)
-        lds_load16(base, static_cast<uint32_t>(min(r0 + RPE * e, n - 1)) * rowb + p16,   // n < 128: below 2^31
-              tile + (e * AT_THR + 64 * w) * 8);
+      for (int e = 0; e < NR / RPE; ++e) {
+        const bf16* dst = tile + (e * AT_THR + 64 * w) * 8;
+        if (r0 + RPE * e < n) {
+          lds_load16(base, off + static_cast<uint32_t>(RPE * e) * rowb, dst);   // n < 128: below 2^31
+        } else {
+          typedef __attribute__((address_space(3))) volatile uint64_t lds_u64;
+          lds_u64* z = (lds_u64*)(dst + 8 * (threadIdx.x & 63));
+          z[0] = 0;
+          z[1] = 0;
+        }
+      }
     }
   }
 };

@@ -331,3 +331,27 @@ def test_attn_heaviest_weight_of_the_first_keys_is_exact(L, d, H, key):
     ref = (w / (w + rows.double()))[:, None, None] * v[key].double()
     # the outputs' own rounding (2^-9) averages out over the values
     assert abs(float((o[rows] * ref).sum() / (ref * ref).sum()) - 1) < 2.0 ** -11
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [2, 512], ids=["64-row workgroups", "128-row workgroups"])
+@pytest.mark.parametrize("rows", [100, 129])
+def test_attn_infinity_in_the_last_row(L, d, H, rows):
+    """A view's last row ends in the middle of a step: an infinite value there
+    makes its own output infinite, and an infinite gradient the values'
+    gradients, neither of them NaN (the step's missing rows are zeros)."""
+    from paper_2608_28158_amd.plan import HartsPlan
+    plan = HartsPlan([-1], [rows], 64)
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    q, k, v, dO = (torch.randn((rows, H, d), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(4))
+    v[-1, :, 3] = float("inf")
+    dO[-1, :, 5] = float("-inf")
+    out = run_attn(L, plan, q, k, v, dO, H, d, 0.5 * d ** -0.5)
+    assert torch.isposinf(out["o"][-1, :, 3]).all()
+    rest = out["o"].clone()
+    rest[:, :, 3] = 0
+    assert torch.isfinite(rest).all()
+    assert torch.isneginf(out["dv"][:, :, 5]).all()
+    rest = out["dv"].clone()
+    rest[:, :, 5] = 0
+    assert torch.isfinite(rest).all()
