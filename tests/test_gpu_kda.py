@@ -255,8 +255,9 @@ def test_kda_backward_unaligned_rows(dtype):
         dq, dk, dg, dbeta = (torch.full_like(t, float("nan")) for t in (q, k, g, beta))
         dv = shift(torch.full_like(v, float("nan")))
         ns = max(sz.n_slots, 1)
-        sq, sk, sg = (torch.empty((ns, H, d), device="cuda") for _ in range(3))
-        sv, sb = shift(torch.empty((ns, H, d), device="cuda")), torch.empty((ns, H), device="cuda")
+        sq, sk, sg = (torch.full((ns, H, d), float("nan"), device="cuda") for _ in range(3))
+        sv = shift(torch.full((ns, H, d), float("nan"), device="cuda"))
+        sb = torch.full((ns, H), float("nan"), device="cuda")
         assert sz.n_slots > 0 and (dv.data_ptr() % 16 != 0) == (shift is off)
         for s0, s1, c0, c1, g0, g1 in reversed(run.rounds):
             _lib.check(run.L.harts_kda_bwd(
@@ -267,11 +268,20 @@ def test_kda_backward_unaligned_rows(dtype):
             _lib.check(run.L.harts_kda_bank_add(_p(run.d_group), g0, g1 - g0, _p(run.d_gseq), H * d * d, _p(dS0),
                                                 _p(dbank), st), "harts_kda_bank_add")
         torch.cuda.synchronize()
-        outs.append([t.clone() for t in (dq, dk, dg, dbeta, dbank)] + [dv.clone(), sv.clone()])
-    for n, (a, b) in enumerate(zip(*outs)):
+        outs.append(dict(dq=dq, dk=dk, dv=dv.clone(), dg=dg, dbeta=dbeta, dbank=dbank, dS0=dS0, sq=sq, sk=sk,
+                         sv=sv.clone(), sg=sg, sb=sb))
+    for n, a in outs[0].items():
+        b = outs[1][n]
+        assert torch.equal(torch.isnan(a), torch.isnan(b)), n
         assert torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), n
-    # rows replayed elsewhere go to the slots, all others to dv
-    assert int(torch.isnan(outs[0][5]).any(-1).any(-1).sum()) == sz.n_multi
+    for out in outs:
+        # rows replayed elsewhere go to the slots (all of them written), all others to the gradients
+        for n in ("dq", "dk", "dv", "dg"):
+            nan = torch.isnan(out[n])
+            assert int(nan.any(-1).any(-1).sum()) == int(nan.all(-1).all(-1).sum()) == sz.n_multi, n
+        assert int(torch.isnan(out["dbeta"]).all(-1).sum()) == sz.n_multi
+        for n in ("dbank", "dS0", "sq", "sk", "sv", "sg", "sb"):
+            assert torch.isfinite(out[n]).all(), n
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
