@@ -15,8 +15,8 @@
 // with those), and steps over the other side 32 or 64 rows at a time; bf16
 // MFMA 16x16x32 with float32 accumulation.  Each step's tiles are loaded
 // straight into one of two LDS buffers while the step before it computes, so
-// a step has one barrier, no LDS writes and no prefetch registers; every
-// fragment read from LDS feeds both halves of the wave.  Every product is
+// a step has one barrier, no LDS writes (but the zeros of rows past a view's
+// end) and no prefetch registers; every fragment read from LDS feeds both halves of the wave.  Every product is
 // issued with the operand roles chosen so that the row the wave owns is the
 // accumulator column (lane % 16): per-row softmax statistics, rescales and
 // outputs then stay in one lane, and a score tile in accumulators is already
@@ -25,9 +25,10 @@
 // masks are evaluated only on steps that cross the causal diagonal.
 //   k_attn_fwd   per (query tile, head): S = Q K^T, online softmax, O = P V;
 //                writes o and the row log-sum-exp;
-//   k_attn_delta per (row, head): delta = dO . O;
 //   k_attn_dq    per (query tile, head): P from the stored log-sum-exp,
-//                dP = dO V^T, dS = P (dP - delta), dQ = scale dS K;
+//                dP = dO V^T, dS = P (dP - delta) with delta = dO . O,
+//                dQ = scale dS K; further workgroups write delta of all rows
+//                for k_attn_dkdv;
 //   k_attn_dkdv  per (key tile, head): over the query tiles that see it,
 //                dV = P^T dO and dK = scale dS^T Q (float32 view rows);
 //   k_attn_gather / k_attn_scatter: compact rows to view rows and back.
@@ -197,8 +198,9 @@ __device__ inline void at_block(int H, int& tile, int& sub, int& h) {
 // 128-query workgroups of d = 128 take 32 keys a step: three of them fit a CU
 // then, and a step's softmax and LDS waits hide behind the products of two
 // other waves (the 64k call: 2,634 us against 2,870 with 64 keys and two
-// workgroups).  At d = 64 three fit with 64 keys too (30,000 rows, 16 heads:
-// 598 us with 32 keys, 574 with 64; four workgroups of either no faster).
+// workgroups).  At d = 64 three and more fit with 64 keys too (30,000 rows, 16
+// heads: 598 us with 32 keys, 574 with 64; held to the registers of four
+// workgroups neither was faster).
 // 64-query ones, used where the chip is not full, take 64 (11.7 us against
 // 13.6 for 2,000 rows of 6 heads of 64).
 // ---------------------------------------------------------------------------
@@ -264,9 +266,8 @@ __global__ __launch_bounds__(AT_THR, NH == 2 ? 3 : 2) void k_attn_fwd(const int3
     for (int j = 0; j < T / 16; ++j)
 #pragma unroll
       for (int a = 0; a < NH; ++a) sc[a][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the product blocks run at raised wave priority, so that the other
-    // wave of the SIMD issues its softmax work while this one feeds the
-    // matrix core
+    // the product blocks run at raised wave priority, so that the SIMD's
+    // other waves do their softmax work while this one feeds the matrix core
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -542,8 +543,9 @@ __global__ __launch_bounds__(AT_THR, D == 64 && NH == 2 ? 4 : 2) void k_attn_dq(
 // TFLOP/s).  What bounds it now: two waves a SIMD, each with a chain of LDS
 // reads, products, exponentials and products a step (MFMA busy 40%, LDS 26%).
 // Three waves of one half each: 7,176 us.  Raised priority around the products
-// 6,500 -> 6,340 us; with one half a wave it cost 10%.  At d = 64 the two
-// halves fit three waves a SIMD (30,000 rows, 16 heads: 1,545 -> 1,355 us).
+// adds 1% to the backward (10,080 -> 10,170 us; nothing at d = 64, and 10% with
+// one half a wave).  At d = 64 the two halves fit three waves a SIMD (30,000
+// rows, 16 heads: 1,545 -> 1,355 us).
 template <int D, int NH>
 __global__ __launch_bounds__(AT_THR, D == 64 ? 3 : 2) void k_attn_dkdv(
     const int32_t* __restrict__ views, const int32_t* __restrict__ kvtiles, int H, float scale,
@@ -629,7 +631,6 @@ __global__ __launch_bounds__(AT_THR, D == 64 ? 3 : 2) void k_attn_dkdv(
         sc[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         dp[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    if (NH == 2) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
@@ -650,7 +651,6 @@ __global__ __launch_bounds__(AT_THR, D == 64 ? 3 : 2) void k_attn_dkdv(
         for (int b = 0; b < NH; ++b) F::mma(dp[b][j], da, vf[b]);
       }
     }
-    if (NH == 2) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const f32x4 lq = *reinterpret_cast<const f32x4*>(sl + 16 * j + 4 * g) * AT_LOG2E;
@@ -690,7 +690,6 @@ __global__ __launch_bounds__(AT_THR, D == 64 ? 3 : 2) void k_attn_dkdv(
       pf[b] = RegB<bf16>::pack(sc[b]);
       sf[b] = RegB<bf16>::pack(dp[b]);
     }
-    if (NH == 2) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int jn = 0; jn < NJ; ++jn) {
       const bf16x8 dt = L::km(sD, 0, 16 * jn, lane);
@@ -700,7 +699,6 @@ __global__ __launch_bounds__(AT_THR, D == 64 ? 3 : 2) void k_attn_dkdv(
 #pragma unroll
       for (int b = 0; b < NH; ++b) F::mma(dk[b][jn], qt, sf[b]);
     }
-    if (NH == 2) __builtin_amdgcn_s_setprio(0);
   }
 #pragma unroll
   for (int b = 0; b < NH; ++b) {

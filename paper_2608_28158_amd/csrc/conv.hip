@@ -54,7 +54,6 @@ template <> struct CV<bf16> {
     x[2] = __uint_as_float(u.y << 16);
     x[3] = __uint_as_float(u.y & 0xffff0000u);
   }
-  __device__ static inline void load(const bf16* p, float* x) { cvt(raw(p), x); }
   __device__ static inline void store(bf16* p, const float* x) {
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     bf16x4 b;
@@ -72,7 +71,6 @@ template <> struct CV<float> {
   __device__ static inline void cvt(const Raw u, float* x) {
     x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
   }
-  __device__ static inline void load(const float* p, float* x) { cvt(raw(p), x); }
   __device__ static inline void store(float* p, const float* x) {
     *reinterpret_cast<float4*>(p) = float4{x[0], x[1], x[2], x[3]};
   }
@@ -85,11 +83,12 @@ template <> struct CV<float> {
 // flight: a wave requests the next CV_G rows before it uses the present ones,
 // and short sub-runs give a small call enough waves.  Measured against one
 // thread per whole run (64 rows backward, 32 forward), every row through the
-// tables: backward of 68,161 x 6,144 bf16, w = 4: 792 -> 566 us (4.4 TB/s of
+// tables: backward of 68,161 x 6,144 bf16, w = 4: 792 -> 518 us (4.9 TB/s of
 // x, dy and dx), of 3,001 x 1,000 float32, w = 3 (47 workgroups before):
-// 53.9 -> 17.7 us; forward 325 -> 316 and 14.4 -> 8.1 us.  Sub-runs of 32
-// rows: 544 and 22.3 us, of 8 rows: 809 and 17.6; two rows at a time: 597 and
-// 15.2 us.
+// 53.9 -> 12.1 us; forward 325 -> 310 and 14.4 -> 8.0 us.  Sub-runs of 32 rows
+// (the forward): 315 us, but 41.9 us instead of 43.2 for 16,000 x 2,048
+// float32, which the cache holds; of 8 rows, or two rows at a time, the
+// backward took longer.
 //
 // The windows over x and dy stay in registers.  A row whose predecessors are
 // the row above it and that row's own needs no table, whatever segments they
