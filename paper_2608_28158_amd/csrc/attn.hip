@@ -539,9 +539,9 @@ __global__ __launch_bounds__(AT_THR, D == 64 && NH == 2 ? 4 : 2) void k_attn_dq(
 // registers, their V rows in LDS: with both in registers, and the next step's
 // tiles on their way through registers, two halves of keys did not fit beside
 // their 128 accumulator registers, and one half read every Q and dO fragment
-// for one product (64k call, 16 heads of 128: 8,021 -> 6,450 us, 624 -> 780
+// for one product (64k call, 16 heads of 128: 8,021 -> 6,250 us, 624 -> 805
 // TFLOP/s).  What bounds it now: two waves a SIMD, each with a chain of LDS
-// reads, products, exponentials and products a step (MFMA busy 40%, LDS 26%).
+// reads, products, exponentials and products a step (MFMA busy 40%, LDS 28%).
 // Three waves of one half each: 7,176 us.  Raised priority around the products
 // adds 1% to the backward (10,080 -> 10,170 us; nothing at d = 64, and 10% with
 // one half a wave).  At d = 64 the two halves fit three waves a SIMD (30,000
